@@ -830,7 +830,11 @@ __device__ void item_z_reduce(const Plan& P, const Args& A, int i) {
 //   A (activations): lane l = 16 g + n holds token row n, inputs
 //     32 ks + 8 g .. + 8 of K-step ks, read from LDS (`ops`, [token][uint4]
 //     with NOPS interleaved sets: 1 for bf16 x, 2 for the bf16 hi/lo parts of
-//     a float32 operand, whose two products are summed).
+//     a float32 operand). With 2 sets a pass has at most 8 token rows, so one
+//     MFMA takes both parts: rows 0..7 the hi parts, rows 8..15 the lo parts
+//     of the same tokens; merge_split adds the two halves of D after the run.
+//     (Two MFMAs and two operand reads per weight operand instead: Qwen3 B=16
+//     expert kernel 39.6 us, the VQ down phase bound by LDS reads.)
 //   W (weights): lane l holds rows 32 ks + 8 g .. + 8 of output column
 //     c0 + 4 n + q for MFMA q = 0..3. For VQ weights this slice is one code
 //     word (d = 8) or two (d = 4) read from the LDS code book; for dense bf16
@@ -843,6 +847,29 @@ __device__ void item_z_reduce(const Plan& P, const Args& A, int i) {
 // MFMA rows are independent, so token rows past nt simply repeat row nt - 1
 // (never stored) instead of branching around the LDS read.
 __device__ __forceinline__ int a_row(int n, int nt) { return min(n, nt - 1); }
+
+// LDS operand index of lane l at K-step `step` (relative to the staged rows)
+// for NOPS sets: the token row's group, of the lo part in rows 8..15 with two.
+template <int NOPS>
+__device__ __forceinline__ int a_index(int l, int nt, int ld, int step) {
+  const int n = l & 15, g = l >> 4;
+  if constexpr (NOPS == 1) return a_row(n, nt) * ld + step * 4 + g;
+  return a_row(n & 7, nt) * ld + (step * 4 + g) * 2 + (n >> 3);
+}
+
+// Adds the two halves of D of a split operand's products: row t (hi) and row
+// t + 8 (lo) sit 32 lanes apart.
+template <int N>
+__device__ __forceinline__ void merge_split(f32x4* acc) {
+#pragma unroll
+  for (int q = 0; q < N; ++q)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const unsigned u = __float_as_uint(acc[q][i]);
+      const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+      acc[q][i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+}
 
 // Scheduling of one K-step: all LDS operand reads first, then the MFMAs, so
 // the reads' latencies overlap instead of each MFMA waiting for its own.
@@ -914,11 +941,8 @@ struct VqPipe {
   __device__ __forceinline__ void step(int ks, const uint32_t (&b)[W], const uint4* __restrict__ cb_s,
                                        const uint4* __restrict__ ops, int ops_ld, int ops_ks0, int nt,
                                        f32x4 acc[4]) {
-    const int l = threadIdx.x & 63, n = l & 15, g = l >> 4;
-    const int oi = a_row(n, nt) * ops_ld + ((ks - ops_ks0) * 4 + g) * NOPS;
-    const uint4 a0 = ops[oi];
-    uint4 a1 = a0;
-    if (NOPS == 2) a1 = ops[oi + 1];
+    const int l = threadIdx.x & 63;
+    const uint4 a0 = ops[a_index<NOPS>(l, nt, ops_ld, ks - ops_ks0)];
     const uint2* cb2 = reinterpret_cast<const uint2*>(cb_s);
     uint4 w[4];
 #pragma unroll
@@ -936,11 +960,8 @@ struct VqPipe {
       }
     }
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      acc[q] = mfma_bf16(a0, w[q], acc[q]);
-      if (NOPS == 2) acc[q] = mfma_bf16(a1, w[q], acc[q]);
-    }
-    sched_step<NOPS + 4 * W, 4 * NOPS>();
+    for (int q = 0; q < 4; ++q) acc[q] = mfma_bf16(a0, w[q], acc[q]);
+    sched_step<1 + 4 * W, 4>();
   }
   __device__ __forceinline__ void run(const uint4* cb_s, const uint4* ops, int ops_ld, int ops_ks0,
                                       int nt, f32x4 acc[4]) {
@@ -1025,9 +1046,7 @@ struct VqPipe2 {
   __device__ __forceinline__ void step(int ks, const uint32_t (&b)[2 * W], const uint4* __restrict__ cb_s,
                                        const uint4* __restrict__ ops, int ops_ld, int ops_ks0, int nt,
                                        f32x4 acc[8]) {
-    const int l = threadIdx.x & 63, n = l & 15, g = l >> 4;
-    const int oi = a_row(n, nt) * ops_ld + ((ks - ops_ks0) * 4 + g) * 2;
-    const uint4 a0 = ops[oi], a1 = ops[oi + 1];
+    const uint4 a0 = ops[a_index<2>(threadIdx.x & 63, nt, ops_ld, ks - ops_ks0)];
     uint4 w[8];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -1035,11 +1054,8 @@ struct VqPipe2 {
       w[4 + q] = word(cb_s, b + W, q);
     }
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      acc[q] = mfma_bf16(a0, w[q], acc[q]);
-      acc[q] = mfma_bf16(a1, w[q], acc[q]);
-    }
-    sched_step<2 + (D == 8 ? 8 : 16), 16>();
+    for (int q = 0; q < 8; ++q) acc[q] = mfma_bf16(a0, w[q], acc[q]);
+    sched_step<1 + (D == 8 ? 8 : 16), 8>();
   }
   __device__ __forceinline__ void run(const uint4* cb_s, const uint4* ops, int ops_ld, int ops_ks0, int nt,
                                       f32x4 acc[8]) {
@@ -1105,23 +1121,13 @@ struct DensePipe {
   }
   __device__ __forceinline__ void step(int ks, const uint2 (&b)[8], const uint4* __restrict__ ops, int ops_ld,
                                        int ops_ks0, int nt, f32x4 acc[4]) {
-    const int l = threadIdx.x & 63, n = l & 15, g = l >> 4;
-    const int oi = a_row(n, nt) * ops_ld + ((ks - ops_ks0) * 4 + g) * NOPS;
-    const uint4 a0 = ops[oi];
-    uint4 a1 = a0;
-    if (NOPS == 2) a1 = ops[oi + 1];
+    const uint4 a0 = ops[a_index<NOPS>(threadIdx.x & 63, nt, ops_ld, ks - ops_ks0)];
     const uint4 w0 = dense_w<0>(b), w1 = dense_w<1>(b), w2 = dense_w<2>(b), w3 = dense_w<3>(b);
     acc[0] = mfma_bf16(a0, w0, acc[0]);
     acc[1] = mfma_bf16(a0, w1, acc[1]);
     acc[2] = mfma_bf16(a0, w2, acc[2]);
     acc[3] = mfma_bf16(a0, w3, acc[3]);
-    if (NOPS == 2) {
-      acc[0] = mfma_bf16(a1, w0, acc[0]);
-      acc[1] = mfma_bf16(a1, w1, acc[1]);
-      acc[2] = mfma_bf16(a1, w2, acc[2]);
-      acc[3] = mfma_bf16(a1, w3, acc[3]);
-    }
-    sched_step<NOPS, 4 * NOPS>();
+    sched_step<1, 4>();
   }
   __device__ __forceinline__ void run(const uint4* ops, int ops_ld, int ops_ks0, int nt, f32x4 acc[4]) {
     if (nks <= PD) {  // every step was primed: no refills
@@ -1146,6 +1152,20 @@ struct DensePipe {
 __device__ __forceinline__ void zero_acc(f32x4 acc[4]) {
 #pragma unroll
   for (int q = 0; q < 4; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+}
+
+// acc += the products of a split operand (their halves of D merged first:
+// rows 8..15 of acc may hold repeats of a token row).
+template <int PD>
+__device__ __forceinline__ void run_split(DensePipe<2, PD>& pipe, const uint4* ops, int ld, int ks0, int nt,
+                                          f32x4 acc[4]) {
+  if (pipe.nks <= 0) return;
+  f32x4 part[4];
+  zero_acc(part);
+  pipe.run(ops, ld, ks0, nt, part);
+  merge_split<4>(part);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) acc[q] += part[q];
 }
 
 // Stores token rows 4g + i < nt of the wave's accumulators with device-scope
@@ -1516,10 +1536,10 @@ __device__ void item_gateup(const Plan& P, const Args& A, const RouteTab& RT, in
     f32x4 acc[4];
     zero_acc(acc);
     const uint4* zs1 = zpre + pj * kXpreZRow;
-    if (lr_first) lr.run(zs1, 1, 0, 1, acc);
+    if (lr_first) run_split(lr, zs1, 1, 0, 1, acc);
     vq.run(cbs, xpre, 1, 0, 1, acc);
     trace_mark(1);
-    if (!lr_first) lr.run(zs1, 1, 0, 1, acc);
+    if (!lr_first) run_split(lr, zs1, 1, 0, 1, acc);
     // every slot of the expert is token 0 (a caller's routing may repeat an expert)
     for (int t = 0; t < R.ne; ++t)
       store_acc(WsAccess(A, P), acc, 1, c0, I, [&](int) { return gu + (((size_t)(R.s0 + t) * 2 + pj) * P.ns + s) * I; });
@@ -1580,7 +1600,7 @@ __device__ void item_gateup(const Plan& P, const Args& A, const RouteTab& RT, in
     trace_mark(0);
     f32x4 acc[4];
     zero_acc(acc);
-    if (lr_first) lr.run(zs, ldz, z0, nt, acc);
+    if (lr_first) run_split(lr, zs, ldz, z0, nt, acc);
     if constexpr (LATE)
       vq.run(cbs, xs, ldx, x0, nt, acc, [&]() {
         if (lr_late) lr.prime(V, I, c0, I, r, z0, z1);
@@ -1588,7 +1608,7 @@ __device__ void item_gateup(const Plan& P, const Args& A, const RouteTab& RT, in
     else
       vq.run(cbs, xs, ldx, x0, nt, acc);
     trace_mark(1);
-    if (!lr_first) lr.run(zs, ldz, z0, nt, acc);
+    if (!lr_first) run_split(lr, zs, ldz, z0, nt, acc);
     store_acc(WsAccess(A, P), acc, nt, c0, I, [&](int t) { return gu + (((size_t)(R.s0 + tg + t) * 2 + pj) * P.ns + s) * I; });
     trace_mark(2);
   }
@@ -1641,6 +1661,7 @@ __device__ __forceinline__ void down_body(const Plan& P, const Args& A, const Ro
     f32x4 acc[4];
     zero_acc(acc);
     run(ps, ld, nt, acc);
+    merge_split<4>(acc);
     store_acc(ws, acc, nt, c0, n_out, [&](int t) { return dst(R.s0 + tg + t); });
   }
 }
@@ -1669,6 +1690,7 @@ __device__ __forceinline__ void down_body_wide(const Plan& P, const Args& A, con
 #pragma unroll
     for (int q = 0; q < NACC; q += 4) zero_acc(acc + q);
     run(ps, ld, nt, acc);
+    merge_split<NACC>(acc);
     finish(ws, acc, nt, R.s0 + tg);
   }
 }
@@ -1947,6 +1969,7 @@ __device__ void item_combine(const Plan& P, const Args& A, const Chain& C, const
     f32x4 acc[4];
     zero_acc(acc);
     bp.run(us, ld, 0, nt, acc);
+    merge_split<4>(acc);
     float* red4 = reinterpret_cast<float*>(smem + combine_lds(P));  // [4 waves][64 lanes][16]
     const int l = tid & 63;
 #pragma unroll
@@ -1972,6 +1995,7 @@ __device__ void item_combine(const Plan& P, const Args& A, const Chain& C, const
     f32x4 acc[4];
     zero_acc(acc);
     bp.run(us, ld, 0, nt, acc);
+    merge_split<4>(acc);
     trace_mark(1);
     const int l = tid & 63, n = l & 15, g = l >> 4;
     const int c = w * 64 + 4 * n;

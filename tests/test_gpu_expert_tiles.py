@@ -1,0 +1,63 @@
+"""GPU parity of the expert tiles at the edges of their token passes.
+
+One expert takes every token (E = 1, top_k = 1), so a tile's passes hold 1 to
+8 token rows and the last pass of a larger batch holds the remainder. Float32
+operands (z, p, u) enter the matrix cores as bf16 hi + lo halves in rows 0..7
+and 8..15 of one product.
+
+Tolerance: a split value is off by at most 2^-18 of itself, so an output is
+off by 2^-18 of the sum of its terms' magnitudes, which for the n = I <= 160
+random-signed terms here is about sqrt(2 n / pi) <= 11 times the result's
+scale: 4e-5, with the float32 sums far below. A lost or misplaced lo half is
+2^-9 of it, a hundred times more.
+"""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle.cardan_oracle as O
+from paper_2609_21137_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+TOL = 4e-5
+
+
+@pytest.fixture(scope="module")
+def C():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_21137_amd import cardan
+    return cardan
+
+
+def _parity(C, H, I, E, k, d, K, r, B, seed, up_only=False):
+    print(f"[tiles] H={H} I={I} E={E} k={k} d={d} K={K} r={r} B={B} up_only={up_only}", flush=True)
+    L = synth.make_layer(H, I, E, d, K, r, seed=seed, up_only=up_only)
+    x = synth.make_input(H, B, seed=seed)
+    act = "relu2_up" if up_only else "silu_glu"
+    y_ref, idx_ref, a_ref, margin = O.moe_layer_factored(x, L, k, d, act=act)
+    assert np.all(margin > 1e-9)
+    shape = C.make_shape(H, I, E, k, d, K, r)
+    ws = C.new_workspace(shape, B)
+    fn = C.moe_layer_relu2 if up_only else C.moe_layer
+    y, idx, wt = fn(shape, C.bf16_tensor(x), C.DeviceLayer.from_numpy(L), ws=ws)
+    torch.cuda.synchronize()
+    assert C.workspace_status(ws) == 0, "an in-kernel wait timed out"
+    assert np.array_equal(idx.cpu().numpy(), idx_ref)
+    err = np.abs(y.cpu().numpy().astype(np.float64) - y_ref).max() / np.abs(y_ref).max()
+    print(f"[tiles] error {err:.2e}", flush=True)
+    assert err <= TOL, err
+
+
+@pytest.mark.parametrize("r", (0, 8, 264))
+@pytest.mark.parametrize("B", (1, 7, 8, 9, 16, 17, 33, 64))
+@pytest.mark.parametrize("d", (2, 4, 8))
+def test_token_passes(C, d, B, r):
+    _parity(C, 192, 96, 1, 1, d, 256, r, B, seed=700 + B)
+
+
+@pytest.mark.parametrize("B", (3, 8, 9))
+def test_token_passes_up_only(C, B):
+    _parity(C, 192, 160, 1, 1, 8, 200, 72, B, seed=740 + B, up_only=True)
