@@ -1365,9 +1365,13 @@ struct Routing {
 // (expert, first slot, slot count) of active expert a, clamped to the valid
 // ranges so that no table content can address memory outside the layer
 __device__ __forceinline__ Routing expert_of(const Plan& P, const RouteTab& RT, int a) {
+  // the record is the same in every lane: held in scalar registers, it keeps
+  // the weight addresses and the pass loops of a tile scalar
   const int4 v = RT.act[a];
-  const int s0 = min(max(v.y, 0), P.S);
-  return {min(max(v.x, 0), P.E - 1), s0, min(max(v.z, 0), P.S - s0)};
+  const int e = __builtin_amdgcn_readfirstlane(v.x), first = __builtin_amdgcn_readfirstlane(v.y);
+  const int n = __builtin_amdgcn_readfirstlane(v.z);
+  const int s0 = min(max(first, 0), P.S);
+  return {min(max(e, 0), P.E - 1), s0, min(max(n, 0), P.S - s0)};
 }
 
 // One code book (K words of D bf16) as 16-byte groups, one per thread, zero
