@@ -226,7 +226,7 @@ int run_layer(const Plan& P, const Args& A, hipStream_t stream, const Chain* cha
   const Chain& C = chain ? *chain : none;
   if (P.total >= 0x80000000ull)  // workspace offsets must stay below the out-of-range marker
     return fail(CARDAN_ERR_UNSUPPORTED, "workspace layout of %zu bytes exceeds 2 GiB", P.total);
-  if (P.lds_route > kLdsMax || P.lds_expert > kLdsMax)
+  if (P.lds_route > kLdsMax || P.lds_expert - book_bytes(P) > kLdsMax)
     return fail(CARDAN_ERR_UNSUPPORTED, "shape needs %zu/%zu bytes of LDS (> %zu)", P.lds_route,
                 P.lds_expert, kLdsMax);
   hipError_t err;

@@ -906,9 +906,46 @@ struct WsAccess {
   }
 };
 
-// NC: copies of the code book in LDS (d = 8): lane l reads copy l % NC, so
-// lanes of one LDS pass collide less on the random code-word rows.
-template <int D, int NOPS, int PD, int NC = 1>
+// The code book in LDS as the tiles read it: word c repeated through a line
+// of 16 << bs bytes, of which each lane reads a copy of its own, so that the
+// lanes of one LDS pass collide less on the random words. The reads of a tile
+// bound its decoding. Measured, clocks of the CU per wave read of 64 random
+// words (8 waves): d = 8 12.4 / 11.8 / 10.7 / 8.2 at bs = 0 / 1 / 2 / 3, d = 4
+// (8 bytes) 6.7 / 6.6 / 6.1 / 4.2, d = 2 (4 bytes) 6.6 / 6.1 / 4.1 / 3.0.
+// LINES false: the words packed one after another (constant shift: one
+// instruction less per word), for batch 1, where few tiles share a CU and the
+// longer store costs more than the reads save, and for d = 4, whose tiles are
+// not bound by these reads.
+template <int D, bool LINES>
+struct BookView {
+  const uint8_t* lane;  // the lane's copy of word 0
+  int sh;               // log2 of the bytes from word to word
+  __device__ __forceinline__ BookView(const uint4* cb, int bs) : lane(reinterpret_cast<const uint8_t*>(cb)) {
+    if constexpr (LINES) {
+      lane += threadIdx.x * 2 * D & ((16 << bs) - 1);
+      sh = 4 + bs;
+    } else {
+      sh = D == 8 ? 4 : D == 4 ? 3 : 2;
+    }
+  }
+  // word of the code in byte q of b
+  __device__ __forceinline__ const uint8_t* at(uint32_t b, int q) const { return lane + (((b >> (8 * q)) & 255u) << sh); }
+  // weight operand of MFMA q: one word (d = 8), or the words of 2 or 4 code rows
+  __device__ __forceinline__ uint4 word(const uint32_t* b, int q) const {
+    if constexpr (D == 8) {
+      return *reinterpret_cast<const uint4*>(at(b[0], q));
+    } else if constexpr (D == 4) {
+      const uint2 lo = *reinterpret_cast<const uint2*>(at(b[0], q));
+      const uint2 hi = *reinterpret_cast<const uint2*>(at(b[1], q));
+      return make_uint4(lo.x, lo.y, hi.x, hi.y);
+    } else {
+      return make_uint4(*reinterpret_cast<const uint32_t*>(at(b[0], q)), *reinterpret_cast<const uint32_t*>(at(b[1], q)),
+                        *reinterpret_cast<const uint32_t*>(at(b[2], q)), *reinterpret_cast<const uint32_t*>(at(b[3], q)));
+    }
+  }
+};
+
+template <int D, int NOPS, int PD, bool LINES>
 struct VqPipe {
   static constexpr int W = 8 / D;  // code rows per lane and K-step (d = 8, 4, 2)
   uint32_t buf[PD][W];
@@ -938,45 +975,32 @@ struct VqPipe {
 #pragma unroll
     for (int u = 0; u < PD; ++u) load(u, buf[u]);
   }
-  __device__ __forceinline__ void step(int ks, const uint32_t (&b)[W], const uint4* __restrict__ cb_s,
+  __device__ __forceinline__ void step(int ks, const uint32_t (&b)[W], const BookView<D, LINES>& cb,
                                        const uint4* __restrict__ ops, int ops_ld, int ops_ks0, int nt,
                                        f32x4 acc[4]) {
     const int l = threadIdx.x & 63;
     const uint4 a0 = ops[a_index<NOPS>(l, nt, ops_ld, ks - ops_ks0)];
-    const uint2* cb2 = reinterpret_cast<const uint2*>(cb_s);
     uint4 w[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      if constexpr (D == 8) {
-        w[q] = cb_s[((b[0] >> (8 * q)) & 255u) * NC + (l & (NC - 1))];
-      } else if constexpr (D == 4) {
-        const uint2 lo = cb2[(b[0] >> (8 * q)) & 255u];
-        const uint2 hi = cb2[(b[1] >> (8 * q)) & 255u];
-        w[q] = make_uint4(lo.x, lo.y, hi.x, hi.y);
-      } else {  // d = 2: four 4-byte code words
-        const uint32_t* cb1 = reinterpret_cast<const uint32_t*>(cb_s);
-        w[q] = make_uint4(cb1[(b[0] >> (8 * q)) & 255u], cb1[(b[1] >> (8 * q)) & 255u],
-                          cb1[(b[2] >> (8 * q)) & 255u], cb1[(b[3] >> (8 * q)) & 255u]);
-      }
-    }
+    for (int q = 0; q < 4; ++q) w[q] = cb.word(b, q);
 #pragma unroll
     for (int q = 0; q < 4; ++q) acc[q] = mfma_bf16(a0, w[q], acc[q]);
     sched_step<1 + 4 * W, 4>();
   }
-  __device__ __forceinline__ void run(const uint4* cb_s, const uint4* ops, int ops_ld, int ops_ks0,
+  __device__ __forceinline__ void run(const BookView<D, LINES>& cb, const uint4* ops, int ops_ld, int ops_ks0,
                                       int nt, f32x4 acc[4]) {
-    run(cb_s, ops, ops_ld, ops_ks0, nt, acc, []() {});
+    run(cb, ops, ops_ld, ops_ks0, nt, acc, []() {});
   }
   // late() runs once when at most PD steps remain (loads for what follows
   // the run go out then, not before the run starts)
   template <typename Late>
-  __device__ __forceinline__ void run(const uint4* cb_s, const uint4* ops, int ops_ld, int ops_ks0,
+  __device__ __forceinline__ void run(const BookView<D, LINES>& cb, const uint4* ops, int ops_ld, int ops_ks0,
                                       int nt, f32x4 acc[4], Late late) {
     if (nks <= PD) {  // every step was primed: no refills
       late();
 #pragma unroll
       for (int u = 0; u < PD; ++u) {
-        if (u < nks) step(ks0 + u, buf[u], cb_s, ops, ops_ld, ops_ks0, nt, acc);
+        if (u < nks) step(ks0 + u, buf[u], cb, ops, ops_ld, ops_ks0, nt, acc);
         __builtin_amdgcn_sched_barrier(0);
       }
       return;
@@ -986,7 +1010,7 @@ struct VqPipe {
 #pragma unroll
       for (int u = 0; u < PD; ++u) {
         const int i = i0 + u;
-        if (i < nks) step(ks0 + i, buf[u], cb_s, ops, ops_ld, ops_ks0, nt, acc);
+        if (i < nks) step(ks0 + i, buf[u], cb, ops, ops_ld, ops_ks0, nt, acc);
         load(i + PD, buf[u]);
         // keep each step's LDS operand reads inside the step: hoisting them
         // across the unrolled pipeline costs registers, not time
@@ -1000,7 +1024,7 @@ struct VqPipe {
 // of two column groups, float32 activations as bf16 hi + lo): each K-step's
 // activation reads serve both sub-tiles. A second sub-tile past n_out reads
 // zeros (its results are never stored).
-template <int D, int PD, int NC = 1>
+template <int D, int PD, bool LINES>
 struct VqPipe2 {
   static constexpr int W = D == 8 ? 1 : 2;
   uint32_t buf[PD][2 * W];
@@ -1033,36 +1057,26 @@ struct VqPipe2 {
 #pragma unroll
     for (int u = 0; u < PD; ++u) load(u, buf[u]);
   }
-  __device__ __forceinline__ uint4 word(const uint4* __restrict__ cb_s, const uint32_t* b, int q) const {
-    if constexpr (D == 8) {
-      return cb_s[((b[0] >> (8 * q)) & 255u) * NC + ((threadIdx.x & 63) & (NC - 1))];
-    } else {
-      const uint2* cb2 = reinterpret_cast<const uint2*>(cb_s);
-      const uint2 lo = cb2[(b[0] >> (8 * q)) & 255u];
-      const uint2 hi = cb2[(b[1] >> (8 * q)) & 255u];
-      return make_uint4(lo.x, lo.y, hi.x, hi.y);
-    }
-  }
-  __device__ __forceinline__ void step(int ks, const uint32_t (&b)[2 * W], const uint4* __restrict__ cb_s,
+  __device__ __forceinline__ void step(int ks, const uint32_t (&b)[2 * W], const BookView<D, LINES>& cb,
                                        const uint4* __restrict__ ops, int ops_ld, int ops_ks0, int nt,
                                        f32x4 acc[8]) {
     const uint4 a0 = ops[a_index<2>(threadIdx.x & 63, nt, ops_ld, ks - ops_ks0)];
     uint4 w[8];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      w[q] = word(cb_s, b, q);
-      w[4 + q] = word(cb_s, b + W, q);
+      w[q] = cb.word(b, q);
+      w[4 + q] = cb.word(b + W, q);
     }
 #pragma unroll
     for (int q = 0; q < 8; ++q) acc[q] = mfma_bf16(a0, w[q], acc[q]);
     sched_step<1 + (D == 8 ? 8 : 16), 8>();
   }
-  __device__ __forceinline__ void run(const uint4* cb_s, const uint4* ops, int ops_ld, int ops_ks0, int nt,
+  __device__ __forceinline__ void run(const BookView<D, LINES>& cb, const uint4* ops, int ops_ld, int ops_ks0, int nt,
                                       f32x4 acc[8]) {
     if (nks <= PD) {  // every step was primed: no refills
 #pragma unroll
       for (int u = 0; u < PD; ++u) {
-        if (u < nks) step(ks0 + u, buf[u], cb_s, ops, ops_ld, ops_ks0, nt, acc);
+        if (u < nks) step(ks0 + u, buf[u], cb, ops, ops_ld, ops_ks0, nt, acc);
         __builtin_amdgcn_sched_barrier(0);
       }
       return;
@@ -1071,7 +1085,7 @@ struct VqPipe2 {
 #pragma unroll
       for (int u = 0; u < PD; ++u) {
         const int i = i0 + u;
-        if (i < nks) step(ks0 + i, buf[u], cb_s, ops, ops_ld, ops_ks0, nt, acc);
+        if (i < nks) step(ks0 + i, buf[u], cb, ops, ops_ld, ops_ks0, nt, acc);
         load(i + PD, buf[u]);
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -1374,32 +1388,39 @@ __device__ __forceinline__ Routing expert_of(const Plan& P, const RouteTab& RT, 
   return {min(max(e, 0), P.E - 1), s0, min(max(n, 0), P.S - s0)};
 }
 
-// One code book (K words of D bf16) as 16-byte groups, one per thread, zero
-// past the book; stored for the item as word c at cb[c] (d = 8) or at the
-// 8-byte slot c of the uint2 view (d = 4). Items load their book before
-// their weight prime and store it with their activation staging.
+// One code book (K words of D bf16, zero words past K): thread c loads word c.
+// Items load their book before their weight prime and store it with their
+// activation staging.
 template <int D>
 __device__ __forceinline__ uint4 book_load(const uint16_t* src, int K) {
-  const int n16 = K * D * 2, byte0 = threadIdx.x * 16;
-  uint4 v = make_uint4(0, 0, 0, 0);
-  if (byte0 + 16 <= n16) {
-    v = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint8_t*>(src) + byte0);
-  } else if (byte0 < n16) {  // ragged end of the book
-    uint16_t e[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int u = 0; byte0 + 2 * u < n16; ++u) e[u] = src[byte0 / 2 + u];
-    v = make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
+  const int c = threadIdx.x;
+  if (c >= K) return make_uint4(0, 0, 0, 0);
+  if constexpr (D == 8) return reinterpret_cast<const uint4*>(src)[c];
+  if constexpr (D == 4) {
+    const uint2 w = reinterpret_cast<const uint2*>(src)[c];
+    return make_uint4(w.x, w.y, w.x, w.y);
   }
-  return v;
+  const uint32_t w = reinterpret_cast<const uint32_t*>(src)[c];
+  return make_uint4(w, w, w, w);
 }
-template <int D>
-__device__ __forceinline__ void book_store(uint4* cb, uint4 v) {
-  if (threadIdx.x < 256 * D / 8) cb[threadIdx.x] = v;
-}
-// NC interleaved copies (d = 8): word w of copy c at w * NC + c
-template <int NC>
-__device__ __forceinline__ void book_store_copies(uint4* cb, uint4 v) {
-#pragma unroll
-  for (int c = 0; c < NC; ++c) cb[threadIdx.x * NC + c] = v;
+
+// Stores the book as BookView reads it: packed, or one line of 16 << bs bytes
+// per word, the word repeated through it. The rotation puts the 16 lanes of an LDS pass on 16 different
+// 16-byte slots (in order of copies they fall on two: 2067 clocks of the CU
+// per book at bs = 3 against 453).
+template <int D, bool LINES>
+__device__ __forceinline__ void book_store(uint4* cb, uint4 v, int bs) {
+  if constexpr (!LINES) {
+    if constexpr (D == 8)
+      cb[threadIdx.x] = v;
+    else if constexpr (D == 4)
+      reinterpret_cast<uint2*>(cb)[threadIdx.x] = make_uint2(v.x, v.y);
+    else
+      reinterpret_cast<uint32_t*>(cb)[threadIdx.x] = v.x;
+    return;
+  }
+  const int c = threadIdx.x, rot = c >> (4 - bs), m = (1 << bs) - 1;
+  for (int i = 0; i <= m; ++i) cb[(c << bs) + ((i + rot) & m)] = v;
 }
 
 // Gate/up tile (a, pj, cg, s): 256 output columns of projection pj over
@@ -1467,7 +1488,7 @@ __device__ void item_gateup_t(const Plan& P, const Args& A, const RouteTab& RT, 
   publish(wsp<int>(A, P.o_gu_tick) + (a * P.ncg + cg) * kTickPad);
 }
 
-template <int D, bool LATE, int NC, bool XP, int PDC>
+template <int D, bool LATE, bool LINES, bool XP, int PDC>
 __device__ void item_gateup(const Plan& P, const Args& A, const RouteTab& RT, int a, int pj, int cg, int s,
                             bool lr_first, uint4* cbs, uint8_t* smem, const uint4* xpre, const uint4* zpre) {
   const Routing R = expert_of(P, RT, a);
@@ -1489,8 +1510,9 @@ __device__ void item_gateup(const Plan& P, const Args& A, const RouteTab& RT, in
   const int* const slot_tok = RT.slot_tok;
   const float* zsrc = (P.flags & F_Z) ? A.z_out : A.z_in;
 
-  VqPipe<D, 1, PDC, NC> vq;
+  VqPipe<D, 1, PDC, LINES> vq;
   DensePipe<2, kPdDense> lr;
+  const BookView<D, LINES> cb(cbs, book_shift(P));
   const int n8x = (x1 - x0) * 4, n8z = (z1 - z0) * 4;  // 8-element groups per token row
   // Activation loads through buffer resources over x [B][H] and z [2][B][r]
   // (written before this kernel): groups past the tile's rows, and z rows
@@ -1531,17 +1553,14 @@ __device__ void item_gateup(const Plan& P, const Args& A, const RouteTab& RT, in
     vq.prime(codes, H / D, I, c0, I, x0, x1);
     lr.prime(V, I, c0, I, r, z0, z1);
     __syncthreads();
-    if constexpr (NC > 1)
-      book_store_copies<NC>(cbs, bk);
-    else
-      book_store<D>(cbs, bk);
+    book_store<D, LINES>(cbs, bk, book_shift(P));
     __syncthreads();
     trace_mark(0);
     f32x4 acc[4];
     zero_acc(acc);
     const uint4* zs1 = zpre + pj * kXpreZRow;
     if (lr_first) run_split(lr, zs1, 1, 0, 1, acc);
-    vq.run(cbs, xpre, 1, 0, 1, acc);
+    vq.run(cb, xpre, 1, 0, 1, acc);
     trace_mark(1);
     if (!lr_first) run_split(lr, zs1, 1, 0, 1, acc);
     // every slot of the expert is token 0 (a caller's routing may repeat an expert)
@@ -1568,10 +1587,7 @@ __device__ void item_gateup(const Plan& P, const Args& A, const RouteTab& RT, in
     vq.prime(codes, H / D, I, c0, I, x0, x1);
     if (!lr_late) lr.prime(V, I, c0, I, r, z0, z1);
     __syncthreads();
-    if constexpr (NC > 1)
-      book_store_copies<NC>(cbs, bk);
-    else
-      book_store<D>(cbs, bk);
+    book_store<D, LINES>(cbs, bk, book_shift(P));
 #pragma unroll
     for (int u = 0; u < kRegStage; ++u) {
       const int i = threadIdx.x + u * kWG;
@@ -1606,11 +1622,11 @@ __device__ void item_gateup(const Plan& P, const Args& A, const RouteTab& RT, in
     zero_acc(acc);
     if (lr_first) run_split(lr, zs, ldz, z0, nt, acc);
     if constexpr (LATE)
-      vq.run(cbs, xs, ldx, x0, nt, acc, [&]() {
+      vq.run(cb, xs, ldx, x0, nt, acc, [&]() {
         if (lr_late) lr.prime(V, I, c0, I, r, z0, z1);
       });
     else
-      vq.run(cbs, xs, ldx, x0, nt, acc);
+      vq.run(cb, xs, ldx, x0, nt, acc);
     trace_mark(1);
     if (!lr_first) run_split(lr, zs, ldz, z0, nt, acc);
     store_acc(WsAccess(A, P), acc, nt, c0, I, [&](int t) { return gu + (((size_t)(R.s0 + tg + t) * 2 + pj) * P.ns + s) * I; });
@@ -1699,7 +1715,7 @@ __device__ __forceinline__ void down_body_wide(const Plan& P, const Args& A, con
   }
 }
 
-template <int D, bool RELU2>
+template <int D, bool LINES, bool RELU2>
 __device__ void item_down_vq(const Plan& P, const Args& A, const RouteTab& RT, int a, int cgx, int s,
                              uint4* cbs, uint8_t* smem) {
   const Routing R = expert_of(P, RT, a);
@@ -1709,7 +1725,7 @@ __device__ void item_down_vq(const Plan& P, const Args& A, const RouteTab& RT, i
   const uint8_t* codes = A.L.codes_down + (size_t)R.e * (I / D) * H;
   float* dn = wsp<float>(A, P.o_dn) + (size_t)s * S * H;
   // d = 2 holds four code rows per K-step: half the steps in flight (same registers as d = 4)
-  VqPipe<D, 2, D == 2 ? kPdVq / 2 : kPdVq> pipe;
+  VqPipe<D, 2, D == 2 ? kPdVq / 2 : kPdVq, LINES> pipe;
   uint4 bk;
   down_body<RELU2>(P, A, R, a, ks0, ks1, c0, H,
             [&]() {
@@ -1717,15 +1733,15 @@ __device__ void item_down_vq(const Plan& P, const Args& A, const RouteTab& RT, i
               __builtin_amdgcn_sched_barrier(0);
               pipe.prime(codes, I / D, H, c0, H, ks0, ks1);
             },
-            [&]() { book_store<D>(cbs, bk); },
-            [&](const uint4* ps, int ld, int nt, f32x4* acc) { pipe.run(cbs, ps, ld, ks0, nt, acc); },
+            [&]() { book_store<D, LINES>(cbs, bk, book_shift(P)); },
+            [&](const uint4* ps, int ld, int nt, f32x4* acc) { pipe.run(BookView<D, LINES>(cbs, book_shift(P)), ps, ld, ks0, nt, acc); },
             [&](int slot) { return dn + (size_t)slot * H; }, smem);
   publish(wsp<int>(A, P.o_dn_done) + (R.e * (P.ncgh + 1) + cgx) * kTickPad);
 }
 
 // VQ down tile over two column groups (cgx, cgx + 1): as item_down_vq, each
 // wave on 64 columns of both groups.
-template <int D, bool RELU2>
+template <int D, bool LINES, bool RELU2>
 __device__ void item_down_vq2(const Plan& P, const Args& A, const RouteTab& RT, int a, int cgx, int s,
                               uint4* cbs, uint8_t* smem) {
   const Routing R = expert_of(P, RT, a);
@@ -1734,7 +1750,7 @@ __device__ void item_down_vq2(const Plan& P, const Args& A, const RouteTab& RT, 
   const int c0 = cgx * kColsPerGroup + (threadIdx.x >> 6) * 64;
   const uint8_t* codes = A.L.codes_down + (size_t)R.e * (I / D) * H;
   float* dn = wsp<float>(A, P.o_dn) + (size_t)s * S * H;
-  VqPipe2<D, kPdVqWide, kBookCopies> pipe;
+  VqPipe2<D, kPdVqWide, LINES> pipe;
   uint4 bk;
   down_body_wide<RELU2, 8>(P, A, R, a, ks0, ks1,
                [&]() {
@@ -1742,8 +1758,8 @@ __device__ void item_down_vq2(const Plan& P, const Args& A, const RouteTab& RT, 
                  __builtin_amdgcn_sched_barrier(0);
                  pipe.prime(codes, I / D, H, c0, H, ks0, ks1);
                },
-               [&]() { book_store_copies<kBookCopies>(cbs, bk); },
-               [&](const uint4* ps, int ld, int nt, f32x4* acc) { pipe.run(cbs, ps, ld, ks0, nt, acc); },
+               [&]() { book_store<D, LINES>(cbs, bk, book_shift(P)); },
+               [&](const uint4* ps, int ld, int nt, f32x4* acc) { pipe.run(BookView<D, LINES>(cbs, book_shift(P)), ps, ld, ks0, nt, acc); },
                [&](const WsAccess& ws, const f32x4* acc, int nt, int slot0) {
                  store_acc(ws, acc, nt, c0, H, [&](int t) { return dn + (size_t)(slot0 + t) * H; });
                  store_acc(ws, acc + 4, nt, c0 + kColsPerGroup, H,
@@ -2174,11 +2190,11 @@ template <int D, int DNW, int MODE, bool CSK, bool XPRE, int VAR>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2), minsize)) void k_expert(Plan P, Args A,
                                                                                                Chain C) {
   constexpr bool RELU2 = (VAR & kVarRelu2) != 0, TBOOK = (VAR & kVarTBook) != 0;
+  constexpr bool LINES = book_lines(D, XPRE);
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-  // the code book of the current item (zero-padded to 256 words), in
-  // kBookCopies copies in the large-batch kernel
-  constexpr int NC = DNW == 2 ? kBookCopies : 1;
-  __shared__ uint4 cbs[MODE == 2 ? 1 : 256 * NC];
+  // the code book of the current item (BookView) at the start of dynamic LDS:
+  // a constant address, so that a read needs no addition for its base
+  uint4* cbs = reinterpret_cast<uint4*>(smem);
   warm_kernargs();
   const int tid = threadIdx.x;
   ItemTrace tr_route;
@@ -2216,11 +2232,12 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2), minsize
       zv[1] = *reinterpret_cast<const float4*>(zsrc + (size_t)pj * P.r + 8 * q + 4);
     }
   }
-  // routing tables at the start of dynamic LDS, item LDS after them
-  uint8_t* item_smem = smem + P.lds_routing;
+  // routing tables after the book, item LDS after them
+  uint8_t* tab = smem + book_bytes(P);
+  uint8_t* item_smem = tab + P.lds_routing;
   const RouteTab RT = wave_routing
-                          ? build_routing_wave(P, (sel_e >= 0 && sel_e < P.E) ? sel_e : -1, sel_w, smem)
-                          : build_routing(P, r_idx, r_w, smem, item_smem, (P.flags & F_ROUTE) != 0);
+                          ? build_routing_wave(P, (sel_e >= 0 && sel_e < P.E) ? sel_e : -1, sel_w, tab)
+                          : build_routing(P, r_idx, r_w, tab, item_smem, (P.flags & F_ROUTE) != 0);
   if constexpr (XPRE) {  // visible to the items after their first barrier
 #pragma unroll
     for (int u = 0; u < 2; ++u)
@@ -2270,7 +2287,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2), minsize
           continue;
         }
       }
-      item_gateup<D, DNW == 2, NC, XPRE, DNW == 2 ? kPdGateUpWide : kPdGateUp>(P, A, RT, t.a, t.pj, t.cg, t.s,
+      item_gateup<D, DNW == 2, LINES, XPRE, DNW == 2 ? kPdGateUpWide : kPdGateUp>(P, A, RT, t.a, t.pj, t.cg, t.s,
                                                                           lr_first, cbs, item_smem, xpre, zpre);
     }
     tr.done(A, P, P.n_pre + jp, 4);
@@ -2283,9 +2300,9 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2), minsize
       if constexpr (MODE != 0)
         item_down_dense<RELU2>(P, A, RT, a, rem / P.nsd, rem % P.nsd, item_smem);
       else if constexpr (DNW == 2)
-        item_down_vq2<D, RELU2>(P, A, RT, a, rem / P.nsd * 2, rem % P.nsd, cbs, item_smem);
+        item_down_vq2<D, LINES, RELU2>(P, A, RT, a, rem / P.nsd * 2, rem % P.nsd, cbs, item_smem);
       else
-        item_down_vq<D, RELU2>(P, A, RT, a, rem / P.nsd, rem % P.nsd, cbs, item_smem);
+        item_down_vq<D, LINES, RELU2>(P, A, RT, a, rem / P.nsd, rem % P.nsd, cbs, item_smem);
       tr.done(A, P, P.n_pre + jp, 5);
     } else {
       item_down_lr<RELU2>(P, A, RT, a, (rem - nvq) / P.nsdl, (rem - nvq) % P.nsdl, item_smem);

@@ -50,7 +50,7 @@ constexpr int kPdGateUpWide = 16;  // gate/up code steps in flight in the large-
                                    // codes per wave, the bytes in flight HBM needs when every tile streams
 constexpr int kPdDense = 2;   // dense K-steps in flight per wave (4 KB each)
 constexpr int kCombineChunk = 16;  // terms per load batch in the combine
-constexpr int kBookCopies = 4;     // code book copies in LDS of the large-batch expert kernel (d = 8)
+constexpr int kBookShiftMax = 3;   // the code book in LDS: 256 lines of up to 16 << kBookShiftMax bytes
 constexpr int kLrDownSteps = 4;    // K-steps of a low-rank down tile when the plan would cut finer
 constexpr int kSplitKRed = 4 * 64 * 16 * 4;  // [4 waves][64 lanes][16] float
 // batch-1 operand area at the end of k_expert's dynamic LDS: x (H <= 4096,
@@ -97,6 +97,7 @@ enum { F_ROUTE = 1, F_Z = 2, F_GROUP = 4, F_EXPERTS = 8,
 // count of timed-out waits
 enum { C_ERR = 0, C_SINK = 1, C_NUM };  // C_SINK: where prefetch loads are folded into one store
 constexpr int kCtrStride = 16;      // ints between counters
+constexpr int kBookShiftPos = 20;   // bits [20, 24) of the plan's flags: log2(line bytes / 16) of the book
 constexpr int kTickPad = 32;        // ints between the tile counters (one 128-byte line each)
 
 struct Plan {
@@ -163,6 +164,15 @@ __host__ __device__ inline int tbook_groups(const Plan& P) {
 __host__ __device__ inline int expert_mode(const Plan& P) {
   return (P.flags & F_GU_DENSE) ? 2 : (P.flags & F_DN_DENSE) ? 1 : 0;
 }
+// The code book in k_expert's LDS (none for all-dense weights): 256 lines of
+// 16 << book_shift bytes, each word repeated through its line.
+__host__ __device__ inline int book_shift(const Plan& P) { return (P.flags >> kBookShiftPos) & 15; }
+__host__ __device__ inline int book_bytes(const Plan& P) {
+  return (P.flags & F_GU_DENSE) ? 0 : 256 * 16 << book_shift(P);
+}
+// Whether the kernel for block length d (xpre: batch 1) reads the book as such
+// lines, or packed (book_shift 0).
+__host__ __device__ constexpr bool book_lines(int d, bool xpre) { return d != 4 && !xpre; }
 // projections with gate/up tiles: gate and up, or up alone
 __host__ __device__ inline int n_proj(const Plan& P) { return (P.flags & F_UP_RELU2) ? 1 : 2; }
 __host__ __device__ inline int gateup_tiles_per_expert(const Plan& P) { return n_proj(P) * P.ncg * P.ns; }

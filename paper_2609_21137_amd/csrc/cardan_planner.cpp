@@ -52,9 +52,9 @@ size_t lds_route(const Plan& P) {
 size_t lds_expert(const Plan& P) {
   const int KSX = P.H / 32, KSZ = ceil_div(P.r, 32), KSD = P.I / 32;
   size_t need = (size_t)P.nt_max * gateup_ld(KSX, KSZ, P.ns, P.ns_v) * 16;
-  // down: p operand rows + a reduction area of 2 float4 per thread
+  // down: p operand rows
   const int ksd = std::max(ks_max(KSD, P.nsd), ks_max(KSD, P.nsdl));
-  need = std::max(need, (size_t)P.nt_max * (ksd * 8 + 1) * 16 + kWG * 2 * 16);
+  need = std::max(need, (size_t)P.nt_max * (ksd * 8 + 1) * 16);
   need = std::max(need, combine_lds(P) + ((P.flags & F_CB_SPLITK) ? kSplitKRed : 0));
   // T-path gate/up tiles: the T rows of their blocks for one token
   if (P.flags & F_TBOOK) need = std::max(need, (size_t)ks_max(KSX, P.ns_v) * (32 / P.d) * P.K * 4);
@@ -248,10 +248,17 @@ Plan make_plan(const cardan_shape* s, int B, int z_sep, int flags) {
   // item LDS, also the grouping scratch at the start of the kernel
   const size_t group_scratch = round256((size_t)2 * P.S * 4 + (size_t)4 * P.E * 4 + 32);
   P.lds_expert = P.lds_routing + std::max(lds_expert(P), group_scratch) + ((P.flags & F_XPRE) ? kXpreBytes : 0);
-  // the large-batch kernel holds kBookCopies code books in static LDS: only
-  // where two workgroups still fit a CU (80 KB each)
-  if ((P.flags & F_DN_WIDE) && P.lds_expert + (size_t)256 * kBookCopies * 16 + 512 > 80 * 1024)
-    P.flags &= ~F_DN_WIDE;
+  // the large-batch kernel only where two workgroups with at least 64-byte
+  // book lines fit a CU (80 KB each)
+  constexpr size_t kLdsHalf = 80 * 1024 - 512;
+  if ((P.flags & F_DN_WIDE) && P.lds_expert + (256 * 16 << 2) > kLdsHalf) P.flags &= ~F_DN_WIDE;
+  // the longest book lines that still let two workgroups share a CU
+  if (mode != 2) {
+    int bs = book_lines(P.d, (P.flags & F_XPRE) != 0) ? kBookShiftMax : 0;
+    while (bs > 0 && P.lds_expert + ((size_t)256 * 16 << bs) > kLdsHalf) --bs;
+    P.flags |= bs << kBookShiftPos;
+    P.lds_expert += book_bytes(P);
+  }
   return P;
 }
 
