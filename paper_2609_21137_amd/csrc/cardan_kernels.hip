@@ -277,7 +277,7 @@ __device__ __forceinline__ float norm_inv(const Plan& P, const Chain& C, int t) 
 // past H read zeros; all of its weights are loaded up front); float64 FMAs of
 // exact bf16 products in row order per token, in groups of 16 rows, then the
 // four waves' partials are added in wave order through LDS.
-__device__ void item_router_chunk(const Plan& P, const Args& A, const Chain& C, int item, int c, int g, int tb,
+__device__ __forceinline__ void item_router_chunk(const Plan& P, const Args& A, const Chain& C, int item, int c, int g, int tb,
                                   uint8_t* smem) {
   constexpr int RW = kRowsRouter / 4;  // rows per wave
   static_assert(RW % 16 == 0, "rows per wave in groups of 16");
@@ -718,7 +718,7 @@ __device__ void select_core(const Plan& P, uint8_t* smem, int lg_cap, double own
 // Select item for token t (see select_core): waits for its token block's
 // router chunks, sums their partials per expert in chunk order (plus the
 // bias) and writes topk_idx / topk_w.
-__device__ void item_select(const Plan& P, const Args& A, int t, uint8_t* smem) {
+__device__ __forceinline__ void item_select(const Plan& P, const Args& A, int t, uint8_t* smem) {
   const int tid = threadIdx.x;
   const int E = P.E, k = P.k;
   double* lg = reinterpret_cast<double*>(smem);  // [E]
@@ -794,7 +794,7 @@ __device__ void tbook_rows(const Plan& P, const Args& A, int t, int pj, int b0, 
   }
 }
 
-__device__ void item_tbook(const Plan& P, const Args& A, int j, uint8_t* smem) {
+__device__ __forceinline__ void item_tbook(const Plan& P, const Args& A, int j, uint8_t* smem) {
   const int d = P.d, nblk = P.H / d, ng = tbook_groups(P), np = n_proj(P);
   const int g = j % ng, rest = j / ng;
   const int pj = np == 2 ? rest % 2 : 1, t = rest / np;
@@ -810,9 +810,15 @@ __device__ void item_tbook(const Plan& P, const Args& A, int j, uint8_t* smem) {
     tbook_rows<2>(P, A, t, pj, b0, nb, xs);
 }
 
-__device__ void item_z_reduce(const Plan& P, const Args& A, int i) {
+__device__ __forceinline__ void item_z_reduce(const Plan& P, const Args& A, int i) {
   const int* zcf = wsp<const int>(A, P.o_zc_flag);
-  wait_all(A, P.n_zc, [&](int f) { return ld_dev(zcf + f * kTickPad) != 0; });
+  const int groups = (P.B + kTokPass - 1) / kTokPass;
+  wait_all(A, z_flags(P), [&](int f) {
+    const int* line = zcf + f * kTickPad;
+    for (int g = 0; g < groups; ++g)
+      if (ld_dev(line + g * kZGroupPad) == 0) return false;
+    return true;
+  });
   const int o = i * kWG + threadIdx.x;
   const int B = P.B, r = P.r;
   if (o < 2 * B * r) {
@@ -1294,13 +1300,19 @@ __device__ __forceinline__ float4 fma4(float w, float4 v, float4 a) {
 // ===========================================================================
 // shared projections on MFMA
 // ===========================================================================
-// z item j: basis pj, 64 columns of z, and four consecutive K-splits of H,
-// one per wave (split 4q + w); the waves' partial U^T x are added in wave
-// order through LDS and item j stores one partial, zp[pj][q][t][col].
-__device__ void item_z(const Plan& P, const Args& A, const Chain& C, int j, uint8_t* smem) {
+// z item j: a group of 16 tokens, basis pj, 64 columns of z, and four
+// consecutive K-splits of H, one per wave (split 4q + w); the waves' partial
+// U^T x are added in wave order through LDS and the item stores one partial,
+// zp[pj][q][t][col], and sets its flag on the line of (pj, columns, q). Bound by
+// its chain of loads (U, x, then the sums), not by U, so the token groups run
+// side by side: one item for every group of a batch of 64 took 12.4 us after
+// the other routing items, four items 4.
+__device__ __forceinline__ void item_z(const Plan& P, const Args& A, const Chain& C, int j, uint8_t* smem) {
   const int tid = threadIdx.x, l = tid & 63, w = tid >> 6;
   const int ncol = (P.r + 63) / 64;
-  const int q = j % P.nq_z, rem = j / P.nq_z;
+  // up to 16 tokens are one group: no division in its way
+  const int zf = z_flags(P), grp = P.B <= kTokPass ? 0 : j / zf, jb = j - grp * zf, tg = grp * kTokPass;
+  const int q = jb % P.nq_z, rem = jb / P.nq_z;
   const int c64 = rem % ncol, pj = rem / ncol;
   const int s = 4 * q + w;
   const bool active = s < P.nch_z;
@@ -1317,56 +1329,53 @@ __device__ void item_z(const Plan& P, const Args& A, const Chain& C, int j, uint
   const int B = P.B, H = P.H, r = P.r;
   const WsAccess ws(A, P);
   DensePipe<1, kPdDense> pipe;
-  for (int tg = 0; tg < B; tg += kTokPass) {
-    const int nt = min(kTokPass, B - tg);
-    if (active) pipe.prime(U, r, c0, r, H, ks0, ks1);
-    if ((P.flags & F_NORM_IN) && tid < nt) zinv[tid] = norm_inv(P, C, tg + tid);
-    __syncthreads();
-    if (active) {  // this wave's own region: lanes stride by 64
-      if (P.flags & F_NORM_IN) {
-        // x = bf16(y * inv_rms), as the router chunks form it
-        const int n8 = (ks1 - ks0) * 4;
-        for (int i = l; i < nt * n8; i += 64) {
-          const int t = i / n8, j8 = i % n8;
-          const float4* yr = reinterpret_cast<const float4*>(C.y_in + (size_t)(tg + t) * H + ks0 * 32 + 8 * j8);
-          const float4 a = yr[0], b = yr[1];
-          const float iv = zinv[t];
-          ops[t * ld + j8] = make_uint4(rne_bf16(a.x * iv) | (rne_bf16(a.y * iv) << 16),
-                                        rne_bf16(a.z * iv) | (rne_bf16(a.w * iv) << 16),
-                                        rne_bf16(b.x * iv) | (rne_bf16(b.y * iv) << 16),
-                                        rne_bf16(b.z * iv) | (rne_bf16(b.w * iv) << 16));
-        }
-      } else {
-        stage_bf16(ops, ld, nt, (ks1 - ks0) * 4,
-                   [&](int t) { return A.x + (size_t)(tg + t) * H + ks0 * 32; }, l, 64);
+  const int nt = min(kTokPass, B - tg);
+  if (active) pipe.prime(U, r, c0, r, H, ks0, ks1);
+  if ((P.flags & F_NORM_IN) && tid < nt) zinv[tid] = norm_inv(P, C, tg + tid);
+  __syncthreads();
+  if (active) {  // this wave's own region: lanes stride by 64
+    if (P.flags & F_NORM_IN) {
+      // x = bf16(y * inv_rms), as the router chunks form it
+      const int n8 = (ks1 - ks0) * 4;
+      for (int i = l; i < nt * n8; i += 64) {
+        const int t = i / n8, j8 = i % n8;
+        const float4* yr = reinterpret_cast<const float4*>(C.y_in + (size_t)(tg + t) * H + ks0 * 32 + 8 * j8);
+        const float4 a = yr[0], b = yr[1];
+        const float iv = zinv[t];
+        ops[t * ld + j8] = make_uint4(rne_bf16(a.x * iv) | (rne_bf16(a.y * iv) << 16),
+                                      rne_bf16(a.z * iv) | (rne_bf16(a.w * iv) << 16),
+                                      rne_bf16(b.x * iv) | (rne_bf16(b.y * iv) << 16),
+                                      rne_bf16(b.z * iv) | (rne_bf16(b.w * iv) << 16));
       }
+    } else {
+      stage_bf16(ops, ld, nt, (ks1 - ks0) * 4,
+                 [&](int t) { return A.x + (size_t)(tg + t) * H + ks0 * 32; }, l, 64);
     }
-    __syncthreads();
-    f32x4 acc[4];
-    zero_acc(acc);
-    if (active) pipe.run(ops, ld, ks0, nt, acc);
-    // lane (n, g) holds token rows 4 g + i, columns c0 + 4 n + qq of MFMA qq
-#pragma unroll
-    for (int qq = 0; qq < 4; ++qq)
-      *reinterpret_cast<float4*>(red + (w * 64 + l) * 16 + 4 * qq) =
-          make_float4(acc[qq][0], acc[qq][1], acc[qq][2], acc[qq][3]);
-    __syncthreads();
-    // thread (i = w, lane l): token row 4 (l >> 4) + i, columns c0 + 4 (l & 15) .. + 3
-    const int n = l & 15, t = 4 * (l >> 4) + w, col = c0 + 4 * n;
-    if (t < nt && col < r) {
-      float v[4];
-#pragma unroll
-      for (int qq = 0; qq < 4; ++qq) {
-        float sum = red[(0 * 64 + l) * 16 + 4 * qq + w];
-#pragma unroll
-        for (int ww = 1; ww < 4; ++ww) sum += red[(ww * 64 + l) * 16 + 4 * qq + w];
-        v[qq] = sum;
-      }
-      ws.st4(ws.off(zp + (((size_t)pj * P.nq_z + q) * B + tg + t) * r + col), make_float4(v[0], v[1], v[2], v[3]));
-    }
-    __syncthreads();
   }
-  set_flag(wsp<int>(A, P.o_zc_flag) + j * kTickPad);
+  __syncthreads();
+  f32x4 acc[4];
+  zero_acc(acc);
+  if (active) pipe.run(ops, ld, ks0, nt, acc);
+  // lane (n, g) holds token rows 4 g + i, columns c0 + 4 n + qq of MFMA qq
+#pragma unroll
+  for (int qq = 0; qq < 4; ++qq)
+    *reinterpret_cast<float4*>(red + (w * 64 + l) * 16 + 4 * qq) =
+        make_float4(acc[qq][0], acc[qq][1], acc[qq][2], acc[qq][3]);
+  __syncthreads();
+  // thread (i = w, lane l): token row 4 (l >> 4) + i, columns c0 + 4 (l & 15) .. + 3
+  const int n = l & 15, t = 4 * (l >> 4) + w, col = c0 + 4 * n;
+  if (t < nt && col < r) {
+    float v[4];
+#pragma unroll
+    for (int qq = 0; qq < 4; ++qq) {
+      float sum = red[(0 * 64 + l) * 16 + 4 * qq + w];
+#pragma unroll
+      for (int ww = 1; ww < 4; ++ww) sum += red[(ww * 64 + l) * 16 + 4 * qq + w];
+      v[qq] = sum;
+    }
+    ws.st4(ws.off(zp + (((size_t)pj * P.nq_z + q) * B + tg + t) * r + col), make_float4(v[0], v[1], v[2], v[3]));
+  }
+  set_flag(wsp<int>(A, P.o_zc_flag) + jb * kTickPad + grp * kZGroupPad);
 }
 
 // ===========================================================================
@@ -2079,6 +2088,24 @@ __device__ __forceinline__ void warm_kernargs() {
 #endif
 }
 
+// The kernel arguments as the kernels' parameters lay them out.
+struct KernArgs {
+  Plan P;
+  Args A;
+  Chain C;
+};
+static_assert(sizeof(KernArgs) == sizeof(Plan) + sizeof(Args) + sizeof(Chain), "no padding between the arguments");
+
+// The kernel arguments read afresh: the compiler cannot carry fields read
+// through one call's pointer, or what it derives from them, to another item
+// or to the start of the kernel.
+__device__ __forceinline__ const KernArgs& kern_args() {
+  typedef const __attribute__((address_space(4))) KernArgs* ptr_t;
+  uint64_t p = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const KernArgs*)(ptr_t)p;
+}
+
 // Each kernel clears the counters of the other kernel of the call before
 // any of them is used again (the stream orders the two kernels): the flags
 // this call's routing items set, and every expert tick of the shape (a call
@@ -2086,6 +2113,12 @@ __device__ __forceinline__ void warm_kernargs() {
 // workspace).
 __device__ __forceinline__ void clear_ints(int* p, int n, int stride = 1) {
   for (int i = threadIdx.x; i < n; i += kWG) p[i * stride] = 0;
+}
+
+__device__ __forceinline__ void clear_z_flags(const Plan& P, const Args& A) {
+  if (P.n_zc > 0)
+    for (int g = 0; g * kTokPass < P.B; ++g)
+      clear_ints(wsp<int>(A, P.o_zc_flag) + g * kZGroupPad, z_flags(P), kTickPad);
 }
 
 // Stacked decode step: a workgroup whose items are done reads its share
@@ -2136,39 +2169,44 @@ __global__ __launch_bounds__(kWG) void k_route(Plan P, Args A, Chain C) {
   for (; j < e_rc; j += gridDim.x) {
     __syncthreads();
     ItemTrace tr;
-    const int nrt = P.nch_r * P.n_eg, jr = j % nrt;
-    item_router_chunk(P, A, C, j, jr % P.nch_r, jr / P.nch_r, j / nrt, smem);
+    const KernArgs& K = kern_args();
+    const int nrt = K.P.nch_r * K.P.n_eg, jr = j % nrt;
+    item_router_chunk(K.P, K.A, K.C, j, jr % K.P.nch_r, jr / K.P.nch_r, j / nrt, smem);
     tr.done(A, P, j, 0);
   }
   for (; j < e_zc; j += gridDim.x) {
     __syncthreads();
     ItemTrace tr;
-    item_z(P, A, C, j - e_rc, smem);
+    const KernArgs& K = kern_args();
+    item_z(K.P, K.A, K.C, j - e_rc, smem);
     tr.done(A, P, j, 1);
   }
   for (; j < e_sel; j += gridDim.x) {
     __syncthreads();
     ItemTrace tr;
-    item_select(P, A, j - e_zc, smem);
+    const KernArgs& K = kern_args();
+    item_select(K.P, K.A, j - e_zc, smem);
     tr.done(A, P, j, 2);
   }
   const int e_zr = P.n_pre - P.n_tb;
   for (; j < e_zr; j += gridDim.x) {
     __syncthreads();
     ItemTrace tr;
-    item_z_reduce(P, A, j - e_sel);
+    const KernArgs& K = kern_args();
+    item_z_reduce(K.P, K.A, j - e_sel);
     tr.done(A, P, j, 3);
   }
   for (; j < P.n_pre; j += gridDim.x) {
     __syncthreads();
-    item_tbook(P, A, j - e_zr, smem);
+    const KernArgs& K = kern_args();
+    item_tbook(K.P, K.A, j - e_zr, smem);
   }
 }
 
 // Clears the routing kernel's flags (after calls that run k_route alone).
 __global__ __launch_bounds__(kWG) void k_route_reset(Plan P, Args A) {
   clear_ints(wsp<int>(A, P.o_rc_flag), P.n_rc, kTickPad);
-  clear_ints(wsp<int>(A, P.o_zc_flag), P.n_zc, kTickPad);
+  clear_z_flags(P, A);
 }
 
 // Expert work of the active experts (count published by k_route): gate/up
@@ -2211,7 +2249,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2), minsize
   }
   if (blockIdx.x == 0) {
     clear_ints(wsp<int>(A, P.o_rc_flag), P.n_rc, kTickPad);
-    clear_ints(wsp<int>(A, P.o_zc_flag), P.n_zc, kTickPad);
+    clear_z_flags(P, A);
   }
   uint4* xpre = reinterpret_cast<uint4*>(smem + P.lds_expert - kXpreBytes);
   uint4* zpre = xpre + kXpreXGroups;

@@ -214,7 +214,7 @@ Plan make_plan(const cardan_shape* s, int B, int z_sep, int flags) {
   // so each workgroup stages them once while it builds its routing tables
   if (mode == 0 && B == 1 && P.H <= 8 * kXpreXGroups) P.flags |= F_XPRE;
 
-  const int z_items = (z_sep ? 2 : 1) * ceil_div(P.r, 64) * P.nq_z;
+  const int z_items = z_flags(P) * ceil_div(B, kTokPass);
   P.n_rc = (flags & F_ROUTE) ? P.nch_r * P.n_eg * ceil_div(B, kRouterTok) : 0;
   P.n_zc = (flags & F_Z) ? z_items : 0;
   P.n_sel = (flags & F_ROUTE) ? B : 0;

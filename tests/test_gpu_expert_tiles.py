@@ -76,3 +76,24 @@ def test_code_book_sizes(C, d, B, K):
 def test_code_book_shorter_lines(C, d):
     """Eight token rows of 1536 inputs leave room for lines of 64 bytes only."""
     _parity(C, 256, 1536, 1, 1, d, 256, 0, 8, seed=780)
+
+
+@pytest.mark.parametrize("separate", (False, True))
+@pytest.mark.parametrize("r", (8, 72, 512))
+@pytest.mark.parametrize("B", (16, 17, 33, 64))
+def test_shared_projection_token_groups(C, B, r, separate):
+    """z = U^T x in groups of 16 tokens, one and several, whole and partial."""
+    H = 320
+    L = synth.make_layer(H, 32, 2, 8, 16, r, seed=840, separate_up_basis=separate)
+    x = synth.make_input(H, B, seed=841)
+    shape = C.make_shape(H, 32, 2, 1, 8, 16, r)
+    ws = C.new_workspace(shape, B)
+    Ug, Uu = C.bf16_tensor(L["U_gate"]), C.bf16_tensor(L["U_up"])
+    for _ in range(2):  # the second call finds the flags as the first left them
+        z = C.shared_proj(shape, C.bf16_tensor(x), Ug, Uu if separate else None, ws=ws)
+    torch.cuda.synchronize()
+    assert C.workspace_status(ws) == 0
+    for got, U in zip(z.cpu().numpy(), (L["U_gate"], L["U_up"])):
+        ref = O.shared_proj(x, U)
+        # 320 float32 sums of exact products
+        assert np.abs(got - ref).max() <= 1e-5 * np.abs(ref).max()
