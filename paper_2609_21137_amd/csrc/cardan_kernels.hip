@@ -460,12 +460,16 @@ __device__ RouteTab build_routing(const Plan& P, const int32_t* idx, const float
   return {act, slot_tok, slot_w, slot_e, tok_slot, s_nact};
 }
 
-// The same tables from at most 64 selections held one per lane of wave 0
+// The same tables from at most 64 selections held one per lane of every wave
 // (lane i: selection i's expert, -1 if none or invalid, and weight). A
 // selection's slot is the number of valid selections of smaller experts plus
 // the earlier ones of its own expert (a stable sort by expert); the active
-// index of an expert is the number of distinct smaller experts.
-__device__ RouteTab build_routing_wave(const Plan& P, int e, float wv, uint8_t* tab) {
+// index of an expert is the number of distinct smaller experts. Each wave
+// counts over 16 selections read from their lanes (one wave counting over all
+// of them took 5.2 us of kernel start at 56 selections) and wave 0 adds the
+// counts; up to 16 selections it needs no others. `scratch`: 256 ints of item
+// LDS, free before the first expert item.
+__device__ RouteTab build_routing_lanes(const Plan& P, int e, float wv, uint8_t* tab, int* scratch) {
   const int S = P.S, k = P.k;
   int4* act = reinterpret_cast<int4*>(tab);
   int* slot_tok = reinterpret_cast<int*>(act + P.max_act);
@@ -473,29 +477,44 @@ __device__ RouteTab build_routing_wave(const Plan& P, int e, float wv, uint8_t* 
   int* slot_e = reinterpret_cast<int*>(slot_w + S);
   int* tok_slot = slot_e + S;
   __shared__ int s_nact;
-  if (threadIdx.x < 64) {
-    const int l = threadIdx.x;
-    int below = 0, same = 0, before = 0;
-    for (int i = 0; i < S; ++i) {
-      const int ei = __builtin_amdgcn_readlane(e, i);
-      below += (int)(ei >= 0) & (int)(ei < e);
-      same += (int)(ei == e);
-      before += (int)(ei == e) & (int)(i < l);
+  const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // counts of at most 64, packed: below (smaller valid experts), same (this
+  // lane's expert), before (of those, the earlier ones)
+  int cnt = 0;
+  if (16 * w < S) {
+    for (int i0 = 16 * w; i0 < 16 * w + 16 && i0 < S; i0 += 4) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int i = i0 + u, ei = __builtin_amdgcn_readlane(e, i);
+        cnt += ei >= 0 && ei < e ? 1 : 0;
+        cnt += ei == e ? (i < l ? 0x10100 : 0x100) : 0;
+      }
     }
-    const int valid = (int)(e >= 0);
-    const unsigned long long firsts = __ballot(valid & (int)(before == 0));
-    int dbelow = 0;
-    for (unsigned long long m = firsts; m; m &= m - 1)
-      dbelow += (int)(__builtin_amdgcn_readlane(e, (int)__builtin_ctzll(m)) < e);
+  }
+  if (S > 16) {
+    scratch[threadIdx.x] = cnt;
+    __syncthreads();
+  }
+  if (threadIdx.x < 64) {
+    if (S > 16) cnt = scratch[l] + scratch[64 + l] + scratch[128 + l] + scratch[192 + l];
+    const int below = cnt & 0xFF, same = (cnt >> 8) & 0xFF, before = cnt >> 16;
+    const bool valid = e >= 0;
+    const int pos = min(below + before, S - 1);
+    // which slots start an expert, as a mask: the valid selections fill slots
+    // 0 .. n - 1
+    const int n = __popcll(__ballot(valid));
+    if (valid) scratch[pos] = before == 0;
+    wave_lds_sync();
+    const unsigned long long firsts = __ballot(l < n && scratch[l] != 0);
     if (l < S) {
-      const int pos = min(below + before, S - 1);
       if (valid) {
         slot_tok[pos] = l / k;
         slot_w[pos] = wv;
         slot_e[pos] = e;
       }
       tok_slot[l] = valid ? pos : -1;
-      if (valid && before == 0 && dbelow < P.max_act) act[dbelow] = make_int4(e, below, same, 0);
+      const int a = __popcll(firsts & ((1ull << below) - 1ull));
+      if (valid && before == 0 && a < P.max_act) act[a] = make_int4(e, below, same, 0);
     }
     if (l == 0) s_nact = min(__popcll(firsts), P.max_act);
   }
@@ -2236,16 +2255,16 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2), minsize
   warm_kernargs();
   const int tid = threadIdx.x;
   ItemTrace tr_route;
-  // Small batches: the selections, one per lane of wave 0, are built into
-  // the routing tables by that wave.
-  const bool wave_routing = P.S <= 64;
+  // Up to 64 selections, held one per lane of every wave: the routing tables
+  // are built from the lanes.
+  const bool lane_routing = P.S <= 64;
   const int32_t* r_idx = (P.flags & F_ROUTE) ? A.topk_idx : A.idx_in;
   const float* r_w = (P.flags & F_ROUTE) ? A.topk_w : A.w_in;
   int sel_e = -1;
   float sel_w = 0.0f;
-  if (wave_routing && tid < P.S) {
-    sel_e = ld_dev(r_idx + tid);
-    sel_w = ld_dev(r_w + tid);
+  if (lane_routing && (tid & 63) < P.S) {
+    sel_e = ld_dev(r_idx + (tid & 63));
+    sel_w = ld_dev(r_w + (tid & 63));
   }
   if (blockIdx.x == 0) {
     clear_ints(wsp<int>(A, P.o_rc_flag), P.n_rc, kTickPad);
@@ -2273,8 +2292,9 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2), minsize
   // routing tables after the book, item LDS after them
   uint8_t* tab = smem + book_bytes(P);
   uint8_t* item_smem = tab + P.lds_routing;
-  const RouteTab RT = wave_routing
-                          ? build_routing_wave(P, (sel_e >= 0 && sel_e < P.E) ? sel_e : -1, sel_w, tab)
+  const RouteTab RT = lane_routing
+                          ? build_routing_lanes(P, (sel_e >= 0 && sel_e < P.E) ? sel_e : -1, sel_w, tab,
+                                                reinterpret_cast<int*>(item_smem))
                           : build_routing(P, r_idx, r_w, tab, item_smem, (P.flags & F_ROUTE) != 0);
   if constexpr (XPRE) {  // visible to the items after their first barrier
 #pragma unroll

@@ -78,6 +78,41 @@ def test_code_book_shorter_lines(C, d):
     _parity(C, 256, 1536, 1, 1, d, 256, 0, 8, seed=780)
 
 
+@pytest.mark.parametrize("B,k", ((1, 1), (2, 8), (3, 8), (7, 7), (8, 8), (13, 5), (16, 4), (65 // 13, 13)))
+def test_routing_tables_from_lanes(C, B, k):
+    """Selections held in lanes: 1 to 64 of them, on both sides of the 16 that
+    one wave counts alone, and the first count beyond (65)."""
+    _parity(C, 128, 64, 40, k, 8, 256, 8, B, seed=800 + B)
+
+
+@pytest.mark.parametrize("S", (3, 17, 40, 64))
+def test_routing_tables_repeats_and_invalid(C, S):
+    """A caller's routing with repeated experts and invalid indices."""
+    H, I, E, d, K, r, k = 128, 64, 5, 8, 256, 8, 1
+    rng = np.random.default_rng(S)
+    L = synth.make_layer(H, I, E, d, K, r, seed=820)
+    x = synth.make_input(H, S, seed=820)
+    idx = rng.integers(-1, E + 1, size=(S, k)).astype(np.int32)
+    idx[0] = 2
+    w = rng.random((S, k)).astype(np.float32)
+    y_ref = np.zeros((S, H))
+    z = np.stack([O.shared_proj(x, L["U_gate"]), O.shared_proj(x, L["U_up"])])
+    xf = O.bf16_to_f64(x)
+    for t in range(S):
+        if 0 <= idx[t, 0] < E:
+            Wg, Wu, Wd = (m for m in O.expert_matrices(L, int(idx[t, 0]), d))
+            g, u = xf[t] @ Wg, xf[t] @ Wu
+            y_ref[t] = w[t, 0] * ((O.silu(g) * u) @ Wd)
+    shape = C.make_shape(H, I, E, k, d, K, r)
+    ws = C.new_workspace(shape, S)
+    y = C.vq_lr_expert_ffn(shape, C.bf16_tensor(x), torch.from_numpy(idx).cuda(), torch.from_numpy(w).cuda(),
+                           torch.from_numpy(z.astype(np.float32)).cuda(), C.DeviceLayer.from_numpy(L), ws=ws)
+    torch.cuda.synchronize()
+    assert C.workspace_status(ws) == 0
+    err = np.abs(y.cpu().numpy() - y_ref).max() / np.abs(y_ref).max()
+    assert err <= 4e-5, err
+
+
 @pytest.mark.parametrize("separate", (False, True))
 @pytest.mark.parametrize("r", (8, 72, 512))
 @pytest.mark.parametrize("B", (16, 17, 33, 64))
