@@ -831,13 +831,7 @@ __device__ __forceinline__ void item_tbook(const Plan& P, const Args& A, int j, 
 
 __device__ __forceinline__ void item_z_reduce(const Plan& P, const Args& A, int i) {
   const int* zcf = wsp<const int>(A, P.o_zc_flag);
-  const int groups = (P.B + kTokPass - 1) / kTokPass;
-  wait_all(A, z_flags(P), [&](int f) {
-    const int* line = zcf + f * kTickPad;
-    for (int g = 0; g < groups; ++g)
-      if (ld_dev(line + g * kZGroupPad) == 0) return false;
-    return true;
-  });
+  wait_all(A, P.n_zc, [&](int f) { return ld_dev(zcf + f * kTickPad) != 0; });
   const int o = i * kWG + threadIdx.x;
   const int B = P.B, r = P.r;
   if (o < 2 * B * r) {
@@ -1319,18 +1313,19 @@ __device__ __forceinline__ float4 fma4(float w, float4 v, float4 a) {
 // ===========================================================================
 // shared projections on MFMA
 // ===========================================================================
-// z item j: a group of 16 tokens, basis pj, 64 columns of z, and four
+// z item j: groups of 16 tokens, basis pj, 64 columns of z, and four
 // consecutive K-splits of H, one per wave (split 4q + w); the waves' partial
 // U^T x are added in wave order through LDS and the item stores one partial,
-// zp[pj][q][t][col], and sets its flag on the line of (pj, columns, q). Bound by
-// its chain of loads (U, x, then the sums), not by U, so the token groups run
-// side by side: one item for every group of a batch of 64 took 12.4 us after
-// the other routing items, four items 4.
+// zp[pj][q][t][col], per group. Bound by its chain of loads (U, x, then the
+// sums), not by U, so the token groups run side by side as far as there are
+// flags: one item for every group of a batch of 64 took 12.4 us after the
+// other routing items, four items 4.
 __device__ __forceinline__ void item_z(const Plan& P, const Args& A, const Chain& C, int j, uint8_t* smem) {
   const int tid = threadIdx.x, l = tid & 63, w = tid >> 6;
   const int ncol = (P.r + 63) / 64;
   // up to 16 tokens are one group: no division in its way
-  const int zf = z_flags(P), grp = P.B <= kTokPass ? 0 : j / zf, jb = j - grp * zf, tg = grp * kTokPass;
+  const int zi = z_items_per_group(P), grp = P.B <= kTokPass ? 0 : j / zi, jb = j - grp * zi;
+  const int tg_step = P.B <= kTokPass ? kTokPass : P.n_zc / zi * kTokPass;
   const int q = jb % P.nq_z, rem = jb / P.nq_z;
   const int c64 = rem % ncol, pj = rem / ncol;
   const int s = 4 * q + w;
@@ -1348,53 +1343,56 @@ __device__ __forceinline__ void item_z(const Plan& P, const Args& A, const Chain
   const int B = P.B, H = P.H, r = P.r;
   const WsAccess ws(A, P);
   DensePipe<1, kPdDense> pipe;
-  const int nt = min(kTokPass, B - tg);
-  if (active) pipe.prime(U, r, c0, r, H, ks0, ks1);
-  if ((P.flags & F_NORM_IN) && tid < nt) zinv[tid] = norm_inv(P, C, tg + tid);
-  __syncthreads();
-  if (active) {  // this wave's own region: lanes stride by 64
-    if (P.flags & F_NORM_IN) {
-      // x = bf16(y * inv_rms), as the router chunks form it
-      const int n8 = (ks1 - ks0) * 4;
-      for (int i = l; i < nt * n8; i += 64) {
-        const int t = i / n8, j8 = i % n8;
-        const float4* yr = reinterpret_cast<const float4*>(C.y_in + (size_t)(tg + t) * H + ks0 * 32 + 8 * j8);
-        const float4 a = yr[0], b = yr[1];
-        const float iv = zinv[t];
-        ops[t * ld + j8] = make_uint4(rne_bf16(a.x * iv) | (rne_bf16(a.y * iv) << 16),
-                                      rne_bf16(a.z * iv) | (rne_bf16(a.w * iv) << 16),
-                                      rne_bf16(b.x * iv) | (rne_bf16(b.y * iv) << 16),
-                                      rne_bf16(b.z * iv) | (rne_bf16(b.w * iv) << 16));
+  for (int tg = grp * kTokPass; tg < B; tg += tg_step) {
+    const int nt = min(kTokPass, B - tg);
+    if (active) pipe.prime(U, r, c0, r, H, ks0, ks1);
+    if ((P.flags & F_NORM_IN) && tid < nt) zinv[tid] = norm_inv(P, C, tg + tid);
+    __syncthreads();
+    if (active) {  // this wave's own region: lanes stride by 64
+      if (P.flags & F_NORM_IN) {
+        // x = bf16(y * inv_rms), as the router chunks form it
+        const int n8 = (ks1 - ks0) * 4;
+        for (int i = l; i < nt * n8; i += 64) {
+          const int t = i / n8, j8 = i % n8;
+          const float4* yr = reinterpret_cast<const float4*>(C.y_in + (size_t)(tg + t) * H + ks0 * 32 + 8 * j8);
+          const float4 a = yr[0], b = yr[1];
+          const float iv = zinv[t];
+          ops[t * ld + j8] = make_uint4(rne_bf16(a.x * iv) | (rne_bf16(a.y * iv) << 16),
+                                        rne_bf16(a.z * iv) | (rne_bf16(a.w * iv) << 16),
+                                        rne_bf16(b.x * iv) | (rne_bf16(b.y * iv) << 16),
+                                        rne_bf16(b.z * iv) | (rne_bf16(b.w * iv) << 16));
+        }
+      } else {
+        stage_bf16(ops, ld, nt, (ks1 - ks0) * 4,
+                   [&](int t) { return A.x + (size_t)(tg + t) * H + ks0 * 32; }, l, 64);
       }
-    } else {
-      stage_bf16(ops, ld, nt, (ks1 - ks0) * 4,
-                 [&](int t) { return A.x + (size_t)(tg + t) * H + ks0 * 32; }, l, 64);
     }
-  }
-  __syncthreads();
-  f32x4 acc[4];
-  zero_acc(acc);
-  if (active) pipe.run(ops, ld, ks0, nt, acc);
-  // lane (n, g) holds token rows 4 g + i, columns c0 + 4 n + qq of MFMA qq
+    __syncthreads();
+    f32x4 acc[4];
+    zero_acc(acc);
+    if (active) pipe.run(ops, ld, ks0, nt, acc);
+    // lane (n, g) holds token rows 4 g + i, columns c0 + 4 n + qq of MFMA qq
 #pragma unroll
-  for (int qq = 0; qq < 4; ++qq)
-    *reinterpret_cast<float4*>(red + (w * 64 + l) * 16 + 4 * qq) =
-        make_float4(acc[qq][0], acc[qq][1], acc[qq][2], acc[qq][3]);
-  __syncthreads();
-  // thread (i = w, lane l): token row 4 (l >> 4) + i, columns c0 + 4 (l & 15) .. + 3
-  const int n = l & 15, t = 4 * (l >> 4) + w, col = c0 + 4 * n;
-  if (t < nt && col < r) {
-    float v[4];
+    for (int qq = 0; qq < 4; ++qq)
+      *reinterpret_cast<float4*>(red + (w * 64 + l) * 16 + 4 * qq) =
+          make_float4(acc[qq][0], acc[qq][1], acc[qq][2], acc[qq][3]);
+    __syncthreads();
+    // thread (i = w, lane l): token row 4 (l >> 4) + i, columns c0 + 4 (l & 15) .. + 3
+    const int n = l & 15, t = 4 * (l >> 4) + w, col = c0 + 4 * n;
+    if (t < nt && col < r) {
+      float v[4];
 #pragma unroll
-    for (int qq = 0; qq < 4; ++qq) {
-      float sum = red[(0 * 64 + l) * 16 + 4 * qq + w];
+      for (int qq = 0; qq < 4; ++qq) {
+        float sum = red[(0 * 64 + l) * 16 + 4 * qq + w];
 #pragma unroll
-      for (int ww = 1; ww < 4; ++ww) sum += red[(ww * 64 + l) * 16 + 4 * qq + w];
-      v[qq] = sum;
+        for (int ww = 1; ww < 4; ++ww) sum += red[(ww * 64 + l) * 16 + 4 * qq + w];
+        v[qq] = sum;
+      }
+      ws.st4(ws.off(zp + (((size_t)pj * P.nq_z + q) * B + tg + t) * r + col), make_float4(v[0], v[1], v[2], v[3]));
     }
-    ws.st4(ws.off(zp + (((size_t)pj * P.nq_z + q) * B + tg + t) * r + col), make_float4(v[0], v[1], v[2], v[3]));
+    __syncthreads();
   }
-  set_flag(wsp<int>(A, P.o_zc_flag) + jb * kTickPad + grp * kZGroupPad);
+  set_flag(wsp<int>(A, P.o_zc_flag) + j * kTickPad);
 }
 
 // ===========================================================================
@@ -2134,12 +2132,6 @@ __device__ __forceinline__ void clear_ints(int* p, int n, int stride = 1) {
   for (int i = threadIdx.x; i < n; i += kWG) p[i * stride] = 0;
 }
 
-__device__ __forceinline__ void clear_z_flags(const Plan& P, const Args& A) {
-  if (P.n_zc > 0)
-    for (int g = 0; g * kTokPass < P.B; ++g)
-      clear_ints(wsp<int>(A, P.o_zc_flag) + g * kZGroupPad, z_flags(P), kTickPad);
-}
-
 // Stacked decode step: a workgroup whose items are done reads its share
 // (part of parts) of
 // the next layer's routing-independent shared tensors (router weights, bases,
@@ -2225,7 +2217,7 @@ __global__ __launch_bounds__(kWG) void k_route(Plan P, Args A, Chain C) {
 // Clears the routing kernel's flags (after calls that run k_route alone).
 __global__ __launch_bounds__(kWG) void k_route_reset(Plan P, Args A) {
   clear_ints(wsp<int>(A, P.o_rc_flag), P.n_rc, kTickPad);
-  clear_z_flags(P, A);
+  clear_ints(wsp<int>(A, P.o_zc_flag), P.n_zc, kTickPad);
 }
 
 // Expert work of the active experts (count published by k_route): gate/up
@@ -2268,7 +2260,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2), minsize
   }
   if (blockIdx.x == 0) {
     clear_ints(wsp<int>(A, P.o_rc_flag), P.n_rc, kTickPad);
-    clear_z_flags(P, A);
+    clear_ints(wsp<int>(A, P.o_zc_flag), P.n_zc, kTickPad);
   }
   uint4* xpre = reinterpret_cast<uint4*>(smem + P.lds_expert - kXpreBytes);
   uint4* zpre = xpre + kXpreXGroups;

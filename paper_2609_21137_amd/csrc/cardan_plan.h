@@ -12,8 +12,9 @@
 // gate/up, down, combine):
 //   router chunks   (64 hidden rows x 64 experts x 4 tokens), float64
 //                   partial logits
-//   z items         (16 tokens, basis, 64 ranks, four consecutive splits of H,
-//                   one per wave): partial U^T x on MFMA, the waves' sums added
+//   z items         (groups of 16 tokens, basis, 64 ranks, four consecutive
+//                   splits of H, one per wave): partial U^T x on MFMA, the
+//                   waves' sums added
 //   select          per token: logits, top-k, gating
 //   z reduce        256 outputs of z = U^T x each
 //   gate/up tiles   (active expert a, gate|up, 256 columns, split of the
@@ -98,9 +99,7 @@ enum { F_ROUTE = 1, F_Z = 2, F_GROUP = 4, F_EXPERTS = 8,
 enum { C_ERR = 0, C_SINK = 1, C_NUM };  // C_SINK: where prefetch loads are folded into one store
 constexpr int kCtrStride = 16;      // ints between counters
 constexpr int kBookShiftPos = 20;   // bits [20, 24) of the plan's flags: log2(line bytes / 16) of the book
-constexpr int kZGroupPad = 8;       // ints between the token groups' flags on a line of z flags
 constexpr int kTickPad = 32;        // ints between the tile counters (one 128-byte line each)
-static_assert(kMaxB <= 4 * kTokPass && 4 * kZGroupPad <= kTickPad, "a z flag line holds every token group");
 
 struct Plan {
   int H, I, E, k, d, K, r, B;
@@ -124,7 +123,7 @@ struct Plan {
   int n_cb;       // combine tiles
   // item counts of this call
   int n_rc, n_zc, n_sel, n_zr, n_pre;
-  int n_rc_flags, n_zc_flags;  // flag slots (shape-wide maxima of n_rc, z_flags)
+  int n_rc_flags, n_zc_flags;  // flag slots (shape-wide maxima of n_rc, n_zc)
   int n_tb;       // projection-code-book items of k_route (F_TBOOK), the last of its items
   // workspace byte offsets
   size_t o_ctr, o_rc_flag, o_zc_flag, o_gu_tick, o_dn_done;  // counters
@@ -175,9 +174,10 @@ __host__ __device__ inline int book_bytes(const Plan& P) {
 // Whether the kernel for block length d (xpre: batch 1) reads the book as such
 // lines, or packed (book_shift 0).
 __host__ __device__ constexpr bool book_lines(int d, bool xpre) { return d != 4 && !xpre; }
-// Flag lines of the z items: one per (basis, 64 ranks, four splits of H), with
-// a flag for every group of kTokPass tokens.
-__host__ __device__ inline int z_flags(const Plan& P) { return (P.z_sep ? 2 : 1) * ((P.r + 63) / 64) * P.nq_z; }
+// z items of one group of tokens: (basis, 64 ranks, four splits of H).
+__host__ __device__ inline int z_items_per_group(const Plan& P) {
+  return (P.z_sep ? 2 : 1) * ((P.r + 63) / 64) * P.nq_z;
+}
 // projections with gate/up tiles: gate and up, or up alone
 __host__ __device__ inline int n_proj(const Plan& P) { return (P.flags & F_UP_RELU2) ? 1 : 2; }
 __host__ __device__ inline int gateup_tiles_per_expert(const Plan& P) { return n_proj(P) * P.ncg * P.ns; }

@@ -214,9 +214,11 @@ Plan make_plan(const cardan_shape* s, int B, int z_sep, int flags) {
   // so each workgroup stages them once while it builds its routing tables
   if (mode == 0 && B == 1 && P.H <= 8 * kXpreXGroups) P.flags |= F_XPRE;
 
-  const int z_items = z_flags(P) * ceil_div(B, kTokPass);
+  // token groups of the shared projection side by side, one flag per item
+  P.n_zc_flags = 2 * ceil_div(kMaxR, 64) * P.nq_z;
+  const int z_group = z_items_per_group(P);
+  P.n_zc = (flags & F_Z) && P.r > 0 ? z_group * std::min(ceil_div(B, kTokPass), P.n_zc_flags / z_group) : 0;
   P.n_rc = (flags & F_ROUTE) ? P.nch_r * P.n_eg * ceil_div(B, kRouterTok) : 0;
-  P.n_zc = (flags & F_Z) ? z_items : 0;
   P.n_sel = (flags & F_ROUTE) ? B : 0;
   P.n_zr = (flags & F_Z) ? ceil_div(2 * B * P.r, kWG) : 0;
   P.n_tb = (P.flags & F_TBOOK) ? B * n_proj(P) * tbook_groups(P) : 0;
@@ -227,7 +229,6 @@ Plan make_plan(const cardan_shape* s, int B, int z_sep, int flags) {
   // the next call's k_route clears them, so every call on a workspace must
   // find them at the same place.
   P.n_rc_flags = P.nch_r * P.n_eg * ceil_div(kMaxB, kRouterTok);
-  P.n_zc_flags = 2 * ceil_div(kMaxR, 64) * P.nq_z;
   size_t o = 0;
   P.o_ctr = o; o = align256(o + (size_t)C_NUM * kCtrStride * 4);
   P.o_rc_flag = o; o = align256(o + (size_t)P.n_rc_flags * kTickPad * 4);
