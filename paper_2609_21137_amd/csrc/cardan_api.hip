@@ -568,10 +568,14 @@ int cardan_moe_layer_noalloc(const cardan_shape* shape, int32_t B, const cardan_
   if ((rc = check_layer(shape, layer, true))) return rc;
   const int z_sep = shape->r > 0 && layer->U_up != layer->U_gate;
   const int flags = F_ROUTE | F_GROUP | F_EXPERTS | (shape->r > 0 ? F_Z : 0);
-  const Plan P = make_plan(shape, B, z_sep, flags);
-  if (P.total > kScratchBytes)
+  // the array takes the layers whose layout with splits by bytes fits it, and
+  // runs them with that layout where the usual one does not fit
+  const Plan least = make_plan(shape, B, z_sep, flags | F_BYTE_SPLITS);
+  if (least.total > kScratchBytes)
     return fail(CARDAN_ERR_WORKSPACE, "layer needs %zu bytes of workspace, more than the %zu-byte scratch array",
-                P.total, kScratchBytes);
+                least.total, kScratchBytes);
+  Plan P = make_plan(shape, B, z_sep, flags);
+  if (P.total > kScratchBytes) P = least;
   void* ws = nullptr;
   bool clear = false;
   if ((rc = scratch_for_call(P, stream, &ws, &clear))) return rc;

@@ -52,7 +52,8 @@ constexpr int kPdGateUpWide = 16;  // gate/up code steps in flight in the large-
 constexpr int kPdDense = 2;   // dense K-steps in flight per wave (4 KB each)
 constexpr int kCombineChunk = 16;  // terms per load batch in the combine
 constexpr int kBookShiftMax = 3;   // the code book in LDS: 256 lines of up to 16 << kBookShiftMax bytes
-constexpr int kLrDownSteps = 4;    // K-steps of a low-rank down tile when the plan would cut finer
+constexpr int kLrDownSteps = 4;    // K-steps of the finest low-rank down tile
+constexpr int kDenseDownSteps = 24;  // most K-steps of a dense down tile of the dense-down form
 constexpr int kSplitKRed = 4 * 64 * 16 * 4;  // [4 waves][64 lanes][16] float
 // batch-1 operand area at the end of k_expert's dynamic LDS: x (H <= 4096,
 // groups of 8 bf16) and z of both projections as bf16 hi/lo pairs per group
@@ -92,7 +93,10 @@ enum { F_ROUTE = 1, F_Z = 2, F_GROUP = 4, F_EXPERTS = 8,
        // input-side projection, T[b][k] = x[b*d .. b*d+d) . cb[k] (float32);
        // a gate/up code tile whose expert has at most kTBookTok tokens sums
        // T[b][J[b][j]] over its blocks instead of decoding code words on MFMA
-       F_TBOOK = 16384 };
+       F_TBOOK = 16384,
+       // tile splits of the compressed forms by bytes alone: the layout that
+       // decides which layers the library's own scratch array takes
+       F_BYTE_SPLITS = 32768 };
 
 // counters at the start of the workspace, one per 64-byte slot: the status
 // count of timed-out waits

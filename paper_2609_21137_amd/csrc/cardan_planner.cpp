@@ -37,6 +37,125 @@ int gateup_ld(int KSX, int KSZ, int ns, int ns_v) {
 
 size_t round256(size_t v) { return (v + 255) & ~(size_t)255; }
 
+constexpr double kSlots = 512.0;  // nominal grid: two workgroups per CU
+
+// Splits of the compressed gate/up tiles and of the down tiles.
+//
+// Gate/up: of the splits of an (expert, projection, 256 columns) into code and
+// low-rank tiles whose expected number fits one round of the nominal grid, the
+// one whose longest tile is shortest; one tile for the whole joint axis where
+// more do not fit. A second round costs each workgroup a tile's set-up again
+// (3 to 4 us of loads before the first product), which longer tiles save:
+// measured per call with the splits that the bytes alone gave and with these,
+// DeepSeek-V2-Lite B=8 69.4 -> 57.0 us (1 code + 2 low-rank -> 1), B=32 119.6 ->
+// 83.8, Gemma-4 B=16 87.2 -> 75.2, OLMoE B=32 82.1 -> 74.2, wide B=2 42.3 -> 34.5
+// (1 + 1 -> 2 + 1). kCode and kLr: microseconds per K-step of a code and a
+// low-rank tile while the grid is full; kSplit: of each split's partial sums
+// in the down tiles' staging. Over 44 shapes and batches these pick the
+// fastest measured split or one within 2 % of it, but for five (3 to 7 %).
+//
+// Down: tiles of about 24 code K-steps (16 at d = 2, which reads four words for
+// one) and 12 low-rank ones (4 KB instead of 1 KB of weights per wave and step)
+// fill many rounds evenly. While finer ones
+// fit one round, the code tiles take as many splits as do, down to 7 K-steps
+// (less than that is set-up), and the low-rank tiles 8 K-steps, or 4 where
+// their ranks fill only two waves.
+void compressed_splits(Plan& P, double exp_act, double npj, int KSX, int KSZ, int KSD, int mode) {
+  const double kCode = P.d == 2 ? 0.2 : 0.13, kLr = 0.6, kSplit = 0.33;
+  const double t1 = exp_act * npj * P.ncg;  // tiles with one split
+  P.ns_v = P.ns = 1;
+  double best = kCode * KSX + kLr * KSZ + kSplit;
+  // (a whole axis of less than a tile's set-up stays one tile)
+  for (int nv = 1; best > 3.0 && nv <= 8 && (nv == 1 || nv * 12 <= KSX); ++nv)
+    for (int nl = 0; nl <= std::min(4, KSZ); ++nl) {
+      // one code and one low-rank tile may exceed the grid by 30 %, priced by
+      // the second round: worth it where both parts are long (Nemotron B=8 80.5
+      // -> 76.7 us, OLMoE B=8 would go 54.2 -> 58.1)
+      const double n = t1 * (nv + nl);
+      const bool second = n > kSlots && n <= 1.3 * kSlots && nv == 1 && nl == 1;
+      if (n > kSlots && !second) continue;
+      // (with no low-rank split the last code tile takes those steps too)
+      const double longest = nl > 0 ? std::max(kCode * KSX / nv, kLr * KSZ / nl) : kCode * KSX / nv + kLr * KSZ;
+      const double cost = longest * (second ? 1.55 : 1.0) + kSplit * (nv + nl);
+      if (cost < best) {
+        best = cost;
+        P.ns_v = nv;
+        P.ns = nv + nl;
+      }
+    }
+  if (mode == 1) {  // dense down tiles, 16 KB per K-step
+    P.nsd = ceil_div(KSD, kDenseDownSteps);
+    while (P.nsd < KSD && exp_act * P.ncgh * (P.nsd + 1) <= kSlots && KSD / (P.nsd + 1) >= kDenseDownSteps / 3) ++P.nsd;
+    return;
+  }
+  P.nsd = std::max(1, (int)lround(KSD / (P.d == 2 ? 16.0 : 24.0)));
+  P.nsdl = P.r > 0 ? std::max(1, (int)lround(KSD / 12.0)) : 1;
+  const int nl_fine = P.r > 0 ? ceil_div(KSD, P.r > 128 ? 8 : kLrDownSteps) : 1;
+  // (where one code tile per column group is enough, fewer low-rank tiles are
+  // tried too before a second round)
+  for (int nl = nl_fine; nl >= (P.nsd == 1 ? 1 : nl_fine); --nl) {
+    int n = 0;
+    while (KSD / (n + 1) >= 7 && exp_act * (P.ncgh * (n + 1) + P.ncgr * nl) <= kSlots) ++n;
+    if (n > 0) {
+      P.nsd = std::max(P.nsd, n);
+      P.nsdl = nl;
+      break;
+    }
+  }
+}
+
+// Splits by bytes, for the all-dense layer and for F_BYTE_SPLITS: the expected
+// active experts' weight bytes spread over the nominal grid, kept between 16
+// and 128 KB per tile, so small batches run every tile in one round and large
+// ones stream long tiles (a VQ down K-step counts double). Dense tiles grow to
+// 512 KB once the nominal tile passes two of 128 KB (a tile's set-up and
+// pipeline drain then recur less often; measured 154 -> 143 us for the dense
+// layer at batch 16). While the items fit the grid and a quarter more, code
+// splits of at most 1, 2 or 4 pipeline depths.
+void byte_splits(Plan& P, double exp_act, double npj, int KSX, int KSZ, int KSD, int mode) {
+  const double code_bytes = mode == 2 ? 256.0 * P.H * 2 : 256.0 * (KSX * 32 / P.d);
+  const double lr_bytes = 256.0 * P.r * 2;
+  const double gu_expert = mode == 2 ? npj * P.H * P.I * 2 : npj * P.H * P.I / P.d + npj * P.I * P.r * 2;
+  const double dn_expert = mode >= 1 ? (double)P.I * P.H * 2 : (double)P.H * P.I / P.d + (double)P.I * P.r * 2;
+  const double nominal = exp_act * (gu_expert + dn_expert) / kSlots;
+  const double tile_max = (mode != 0 && nominal > 2 * 128.0 * 1024 ? 512.0 : 128.0) * 1024;
+  double tile = fmin(tile_max, fmax(16.0 * 1024, nominal));
+  auto splits = [&](double bytes, int max_splits) {
+    return std::max(1, std::min(max_splits, (int)lround(bytes / tile)));
+  };
+  for (;;) {
+    if (tile >= 0.75 * (code_bytes + lr_bytes)) {
+      P.ns_v = P.ns = 1;  // one tile holds the whole joint axis
+    } else {
+      P.ns_v = splits(code_bytes, KSX);
+      P.ns = P.ns_v + (KSZ > 0 ? splits(lr_bytes, KSZ) : 0);
+    }
+    P.nsd = mode >= 1 ? splits(256.0 * P.I * 2, KSD) : splits(2.0 * 256.0 * P.I / P.d, KSD);
+    P.nsdl = P.r > 0 ? splits((double)std::min(P.r, kColsPerGroup) * P.I * 2, KSD) : 1;
+    const double items = exp_act * (npj * P.ncg * P.ns + P.ncgh * P.nsd + P.ncgr * P.nsdl);
+    if (items <= kSlots || tile >= tile_max) break;
+    tile *= 1.05;
+  }
+  if (P.ns > 1) {
+    const int pd = mode == 2 ? kPdDenseW : kPdVq;
+    const int nl_fine = KSZ > 0 ? ceil_div(KSZ, kPdDense) : 0, nl_keep = P.ns - P.ns_v;
+    bool done = false;
+    for (int mult = 1; mult <= 4 && !done; mult *= 2) {
+      const int nv = std::max(P.ns_v, ceil_div(KSX, pd * mult));
+      for (const int nl : {nl_fine, nl_keep}) {
+        const double items = exp_act * (npj * P.ncg * (nv + nl) + P.ncgh * P.nsd + P.ncgr * P.nsdl);
+        if (items <= 1.25 * kSlots) {
+          P.ns_v = nv;
+          P.ns = nv + nl;
+          done = true;
+          break;
+        }
+      }
+    }
+  }
+  P.nsdl = std::min(P.nsdl, ceil_div(KSD, kLrDownSteps));
+}
+
 // Dynamic LDS of k_route for a plan.
 size_t lds_route(const Plan& P) {
   const int KSX = P.H / 32;
@@ -61,11 +180,7 @@ size_t lds_expert(const Plan& P) {
   return round256(need);
 }
 
-}  // namespace
-
-// Launch plan, item counts and workspace layout; depends only on
-// (shape, B, z_sep, flags). F_GU_DENSE plans take r = 0.
-Plan make_plan(const cardan_shape* s, int B, int z_sep, int flags) {
+Plan plan_once(const cardan_shape* s, int B, int z_sep, int flags) {
   Plan P;
   memset(&P, 0, sizeof P);
   P.H = s->H; P.I = s->I; P.E = s->E; P.k = s->top_k; P.d = s->d; P.K = s->K; P.r = s->r;
@@ -83,89 +198,41 @@ Plan make_plan(const cardan_shape* s, int B, int z_sep, int flags) {
   // keeps the large-batch kernel's operand staging small enough for its
   // code book copies
   P.nt_max = B > 8 ? 8 : B;
-  // combine tiles of up to B/16 tokens: sixteen per column group at large
-  // batches, so the final gather is spread over more workgroups (one token
-  // per tile at batch 16: the Nemotron-shaped layer 119.9 -> 117.9 us, the
-  // Qwen3 one unchanged, against B/8)
-  P.tpc = std::min(kTokPass, ceil_div(B, 16));
+  // combine tiles of few tokens, so that the final gather is spread over more
+  // workgroups: B/32 each (OLMoE B=32 1 token instead of 2: 2 us less), and up
+  // to two where the low-rank gather is short (r <= 128: one token each is 1 %
+  // slower there)
+  P.tpc = (flags & F_BYTE_SPLITS) ? ceil_div(B, 16) : P.r > 128 ? ceil_div(B, 32) : std::min(2, ceil_div(B, 16));
   const int KSX = P.H / 32, KSZ = ceil_div(P.r, 32), KSD = P.I / 32;
   P.nch_z = std::max(1, KSX / 2);                  // two K-steps of U per z unit (one wave)
   P.nq_z = ceil_div(P.nch_z, 4);                   // four units per z item, summed in LDS
-  // Tile sizes: the expected active experts' weight bytes spread over a
-  // nominal grid of 512 workgroups (2 per CU), kept between 16 and 64 KB per
-  // tile, so small batches run every tile in one round and large ones stream
-  // long tiles. Bytes per tile: a gate/up (expert, projection, 256 columns)
-  // holds 256 (H/d) code bytes and 256 r * 2 coefficient bytes; a VQ down
-  // (expert, 256 columns) 256 I/d; a low-rank down (expert, <= 256 ranks)
-  // min(r, 256) I * 2. Dense bf16 weights: 256 H * 2 per gate/up and
-  // 256 I * 2 per down (expert, 256 columns).
   const double exp_act = fmax(1.0, P.E * (1.0 - pow(1.0 - (double)P.k / P.E, (double)B)));
   const double npj = n_proj(P);  // gate and up, or up alone
-  const double gu_expert = mode == 2 ? npj * P.H * P.I * 2 : npj * P.H * P.I / P.d + npj * P.I * P.r * 2;
-  const double dn_expert = mode >= 1 ? (double)P.I * P.H * 2 : (double)P.H * P.I / P.d + (double)P.I * P.r * 2;
-  const double per_expert = gu_expert + dn_expert;
-  // A VQ down K-step costs twice a gate/up one (p enters as hi + lo), so its
-  // bytes count double. While the expected items exceed the nominal grid
-  // the tile grows (small batches then run in one round).
-  // Dense-weight forms stream 4-16x the bytes: once the nominal tile passes
-  // two 128 KB tiles, their tiles grow to 512 KB (a tile's set-up and pipeline
-  // drain then recur less often; measured 154 -> 143 us for the dense layer
-  // at batch 16, while small batches keep the one-round 128 KB tiles).
-  const double nominal = exp_act * per_expert / 512.0;
-  const double tile_max = (mode != 0 && nominal > 2 * 128.0 * 1024 ? 512.0 : 128.0) * 1024;
-  double tile = fmin(tile_max, fmax(16.0 * 1024, nominal));
-  auto splits = [&](double bytes, int max_splits) {
-    return std::max(1, std::min(max_splits, (int)lround(bytes / tile)));
-  };
   P.ncg = ceil_div(P.I, kColsPerGroup);
   P.ncgh = ceil_div(P.H, kColsPerGroup);
   P.ncgr = mode == 0 ? ceil_div(P.r, kColsPerGroup) : 0;  // low-rank down column groups
-  for (;;) {
-    // code (or dense) splits and low-rank splits of a gate/up (expert, 256 columns)
-    const double code_bytes = mode == 2 ? 256.0 * P.H * 2 : 256.0 * (KSX * 32 / P.d);
-    const double lr_bytes = 256.0 * P.r * 2;
-    if (tile >= 0.75 * (code_bytes + lr_bytes)) {
-      P.ns_v = P.ns = 1;  // one tile holds the whole joint axis
-    } else {
-      P.ns_v = splits(code_bytes, KSX);
-      P.ns = P.ns_v + (KSZ > 0 ? splits(lr_bytes, KSZ) : 0);
-    }
-    P.nsd = mode >= 1 ? splits(256.0 * P.I * 2, KSD) : splits(2.0 * 256.0 * P.I / P.d, KSD);
-    P.nsdl = P.r > 0 ? splits((double)std::min(P.r, kColsPerGroup) * P.I * 2, KSD) : 1;
-    const double items = exp_act * (npj * P.ncg * P.ns + P.ncgh * P.nsd + P.ncgr * P.nsdl);
-    if (items <= 512.0 || tile >= tile_max) break;
-    tile *= 1.05;
+  P.nsdl = 1;
+  const bool by_bytes = mode == 2 || (P.flags & F_BYTE_SPLITS);
+  if (by_bytes)
+    byte_splits(P, exp_act, npj, KSX, KSZ, KSD, mode);
+  else
+    compressed_splits(P, exp_act, npj, KSX, KSZ, KSD, mode);
+  // routing tables: active-expert records and four per-slot arrays
+  P.lds_routing = round256((size_t)P.max_act * 16 + (size_t)4 * P.S * 4);
+  const size_t budget = by_bytes ? kLdsBudget : std::min(kLdsBudget, kLdsMax - std::min(kLdsMax, P.lds_routing));
+  // Operand staging that does not fit LDS: split the codes (up to four ways)
+  // before halving the token rows of a pass (down to 4), since experts with
+  // more tokens than one pass stream and decode their weights again per pass
+  // (the wide layer with 8 hot experts at B = 8: 78 us in passes of 4 rows, 55
+  // in two splits of 8).
+  auto staging = [&]() { return (size_t)P.nt_max * gateup_ld(KSX, KSZ, P.ns, P.ns_v) * 16; };
+  while (!by_bytes && P.nt_max > 4 && P.ns_v < std::min(4, KSX) && staging() > budget) {
+    ++P.ns_v;
+    ++P.ns;
   }
-  // Latency shape: while the item count fits the nominal grid (with a
-  // quarter more for a short second round), code splits of at most L K-steps
-  // for the smallest L in {1, 2, 4} x the pipeline depth, with low-rank splits
-  // of kPdDense steps where they fit too, else as many as the byte balance
-  // gave. At large r the byte balance alone leaves one code split of H/32
-  // steps, a chain of H/32/kPdVq dependent pipeline refills (r = 384 at B=1:
-  // 35.7 us).
-  if (P.ns > 1) {
-    const int pd = mode == 2 ? kPdDenseW : kPdVq;
-    const int nl_fine = KSZ > 0 ? ceil_div(KSZ, kPdDense) : 0, nl_keep = P.ns - P.ns_v;
-    bool done = false;
-    for (int mult = 1; mult <= 4 && !done; mult *= 2) {
-      const int nv = std::max(P.ns_v, ceil_div(KSX, pd * mult));
-      for (const int nl : {nl_fine, nl_keep}) {
-        const double items = exp_act * (npj * P.ncg * (nv + nl) + P.ncgh * P.nsd + P.ncgr * P.nsdl);
-        if (items <= 1.25 * 512.0) {
-          P.ns_v = nv;
-          P.ns = nv + nl;
-          done = true;
-          break;
-        }
-      }
-    }
-  }
-  // token rows staged per pass: halve (down to 4) before splitting K further
-  // to fit the operand staging into LDS; experts with more tokens than one
-  // pass stream their weights again per pass (rare at these sizes)
-  while (P.nt_max > 4 && (size_t)P.nt_max * gateup_ld(KSX, KSZ, P.ns, P.ns_v) * 16 > kLdsBudget)
+  while (P.nt_max > 4 && (size_t)P.nt_max * gateup_ld(KSX, KSZ, P.ns, P.ns_v) * 16 > budget)
     P.nt_max = (P.nt_max + 1) / 2;
-  while (P.ns_v < KSX && (size_t)P.nt_max * gateup_ld(KSX, KSZ, P.ns, P.ns_v) * 16 > kLdsBudget) {
+  while (P.ns_v < KSX && (size_t)P.nt_max * gateup_ld(KSX, KSZ, P.ns, P.ns_v) * 16 > budget) {
     if (P.ns == P.ns_v && KSZ > 0) ++P.ns;  // give the low-rank steps their own split first
     else {
       ++P.ns_v;
@@ -191,11 +258,8 @@ Plan make_plan(const cardan_shape* s, int B, int z_sep, int flags) {
     P.ns = P.ns_v + nl;
   }
   auto down_fits = [&](int n) {
-    return (size_t)P.nt_max * (ks_max(KSD, n) * 8 + 1) * 16 + kWG * 2 * 16 <= kLdsBudget;
+    return (size_t)P.nt_max * (ks_max(KSD, n) * 8 + 1) * 16 + kWG * 2 * 16 <= budget;
   };
-  // low-rank down tiles cover at least kLrDownSteps K-steps (their weights
-  // load while they wait): fewer partials of u_e for the combine to sum
-  P.nsdl = std::min(P.nsdl, ceil_div(KSD, kLrDownSteps));
   while (P.nsd < KSD && !down_fits(P.nsd)) ++P.nsd;
   while (P.nsdl < KSD && !down_fits(P.nsdl)) ++P.nsdl;
   // Items for more than two rounds of the nominal grid (throughput-bound):
@@ -203,7 +267,7 @@ Plan make_plan(const cardan_shape* s, int B, int z_sep, int flags) {
   // reads serve twice the columns and the down tiles take half the
   // workgroup slots (fewer rounds, longer tiles)
   const double items_all = exp_act * (npj * P.ncg * P.ns + P.ncgh * P.nsd + P.ncgr * P.nsdl);
-  if (mode == 0 && items_all > 2 * 512.0 && P.ncgh > 1 && P.d == 8 && !(P.flags & F_TBOOK)) P.flags |= F_DN_WIDE;
+  if (mode == 0 && items_all > 2 * kSlots && P.ncgh > 1 && P.d == 8 && !(P.flags & F_TBOOK)) P.flags |= F_DN_WIDE;
 
   // Small batches at ranks above 128: B^T u streams more of B than a
   // combine tile primes before its wait, so the tiles shrink to 64 columns
@@ -244,8 +308,6 @@ Plan make_plan(const cardan_shape* s, int B, int z_sep, int flags) {
   if (P.flags & F_TBOOK) o = tbook_offset(P) + tbook_bytes(P);
   P.total = o;
   P.lds_route = lds_route(P);
-  // routing tables: active-expert records and four per-slot arrays
-  P.lds_routing = round256((size_t)P.max_act * 16 + (size_t)4 * P.S * 4);
   // item LDS, also the grouping scratch at the start of the kernel
   const size_t group_scratch = round256((size_t)2 * P.S * 4 + (size_t)4 * P.E * 4 + 32);
   P.lds_expert = P.lds_routing + std::max(lds_expert(P), group_scratch) + ((P.flags & F_XPRE) ? kXpreBytes : 0);
@@ -261,6 +323,19 @@ Plan make_plan(const cardan_shape* s, int B, int z_sep, int flags) {
     P.lds_expert += book_bytes(P);
   }
   return P;
+}
+
+}  // namespace
+
+// Launch plan, item counts and workspace layout; depends only on
+// (shape, B, z_sep, flags). F_GU_DENSE plans take r = 0. A plan whose partial
+// sums would pass the 2 GiB that offsets reach, or whose term tables the LDS
+// limit, is made again with the splits by bytes.
+Plan make_plan(const cardan_shape* s, int B, int z_sep, int flags) {
+  const Plan P = plan_once(s, B, z_sep, flags);
+  const bool fits = P.total < 0x80000000ull && P.lds_expert - book_bytes(P) <= kLdsMax;
+  if (fits || (flags & F_BYTE_SPLITS)) return P;
+  return plan_once(s, B, z_sep, flags | F_BYTE_SPLITS);
 }
 
 }  // namespace cardan

@@ -132,3 +132,19 @@ def test_shared_projection_token_groups(C, B, r, separate):
         ref = O.shared_proj(x, U)
         # 320 float32 sums of exact products
         assert np.abs(got - ref).max() <= 1e-5 * np.abs(ref).max()
+
+
+def test_noalloc_smaller_layout(C):
+    """A layer whose usual layout exceeds the library's scratch array, but not
+    the one with splits by bytes: it runs there with the latter and gives the
+    usual result up to the order of the float32 sums."""
+    H, I, E, k, d, K, r, B = 832, 1600, 8, 6, 4, 128, 112, 44
+    L = C.DeviceLayer.from_numpy(synth.make_layer(H, I, E, d, K, r, seed=860))
+    x = C.bf16_tensor(synth.make_input(H, B, seed=860))
+    shape = C.make_shape(H, I, E, k, d, K, r)
+    assert C.workspace_bytes(shape, B) > 16 << 20
+    y, idx, _ = C.moe_layer(shape, x, L)
+    y2, idx2, _ = C.moe_layer_noalloc(shape, x, L)
+    torch.cuda.synchronize()
+    assert torch.equal(idx, idx2)
+    assert float((y - y2).abs().max()) <= 2e-5 * float(y.abs().max())
