@@ -362,10 +362,16 @@ __device__ __forceinline__ void item_router_chunk(const Plan& P, const Args& A, 
 // from the B*k selections; the construction is deterministic, so all
 // workgroups agree on every slot number.
 struct RouteTab {
-  const int4* act;       // [nact] (expert, first slot, slot count, 0), experts ascending
+  // [nact] records (expert, first slot, slot count, records of the expert),
+  // experts ascending. An expert with more slots than a pass stages has a
+  // record per pass, so that the passes are tiles of their own on other
+  // workgroups: in one tile they ran one after another, and a few experts of 9
+  // and more tokens set the end of the gate/up and of the down phase (longest
+  // gate/up tile at Qwen3 B=64 35 us, the median 18).
+  const int4* act;
   const int* slot_tok;   // [S] token of each slot
   const float* slot_w;   // [S] gating weight of each slot
-  const int* slot_e;     // [S] expert of each slot
+  const int* slot_e;     // [S] expert of each slot | its records << 16
   const int* tok_slot;   // [S] slot of selection (t, j), -1 if the expert is invalid
   int nact;
 };
@@ -381,7 +387,7 @@ __device__ RouteTab build_routing(const Plan& P, const int32_t* idx, const float
                                   uint8_t* scratch, bool distinct) {
   const int tid = threadIdx.x, E = P.E, S = P.S, k = P.k;
   int4* act = reinterpret_cast<int4*>(tab);
-  int* slot_tok = reinterpret_cast<int*>(act + P.max_act);
+  int* slot_tok = reinterpret_cast<int*>(act + max_records(P));
   float* slot_w = reinterpret_cast<float*>(slot_tok + S);
   int* slot_e = reinterpret_cast<int*>(slot_w + S);
   int* tok_slot = slot_e + S;
@@ -413,8 +419,9 @@ __device__ RouteTab build_routing(const Plan& P, const int32_t* idx, const float
   }
   __syncthreads();
   // one scan gives both the first slot of every expert (low 16 bits) and
-  // its index among the active experts (high bits)
-  for (int e = tid; e < E; e += kWG) s_cnt[e] += (s_cnt[e] > 0) << 16;
+  // its first record (high bits)
+  const int rs = record_shift(P), rows = 1 << rs;
+  for (int e = tid; e < E; e += kWG) s_cnt[e] += (s_cnt[e] + rows - 1) >> rs << 16;
   __syncthreads();
   int* s_cnt0 = s_tmp + 4;  // [E] counts kept for the records
   for (int e = tid; e < E; e += kWG) s_cnt0[e] = s_cnt[e] & 0xFFFF;
@@ -423,9 +430,11 @@ __device__ RouteTab build_routing(const Plan& P, const int32_t* idx, const float
   for (int e = tid; e < E; e += kWG) {
     const int c = s_cnt0[e];
     const int a = s_cnt[e] >> 16;
-    if (c > 0 && a < P.max_act) act[a] = make_int4(e, s_cnt[e] & 0xFFFF, c, 0);
+    const int nr = (c + rows - 1) >> rs, first = s_cnt[e] & 0xFFFF;
+    for (int i = 0; i < nr && a + i < max_records(P); ++i)
+      act[a + i] = make_int4(e, first + i * rows, min(rows, c - i * rows), nr);
   }
-  if (tid == 0) s_nact = min(total >> 16, P.max_act);
+  if (tid == 0) s_nact = min(total >> 16, max_records(P));
   trace_mark(2);
   // slot of selection i: the expert's first slot + the number of earlier
   // selections of the same expert (earlier tokens from the token mask when
@@ -452,7 +461,7 @@ __device__ RouteTab build_routing(const Plan& P, const int32_t* idx, const float
     const int pos = min((s_cnt[e] & 0xFFFF) + rank, S - 1);
     slot_tok[pos] = i / k;
     slot_w[pos] = s_w[i];
-    slot_e[pos] = e;
+    slot_e[pos] = e | (s_cnt0[e] + rows - 1) >> rs << 16;
     tok_slot[i] = pos;
   }
   __syncthreads();
@@ -463,8 +472,8 @@ __device__ RouteTab build_routing(const Plan& P, const int32_t* idx, const float
 // The same tables from at most 64 selections held one per lane of every wave
 // (lane i: selection i's expert, -1 if none or invalid, and weight). A
 // selection's slot is the number of valid selections of smaller experts plus
-// the earlier ones of its own expert (a stable sort by expert); the active
-// index of an expert is the number of distinct smaller experts. Each wave
+// the earlier ones of its own expert (a stable sort by expert); its record is
+// the number of slots before it that start one. Each wave
 // counts over 16 selections read from their lanes (one wave counting over all
 // of them took 5.2 us of kernel start at 56 selections) and wave 0 adds the
 // counts; up to 16 selections it needs no others. `scratch`: 256 ints of item
@@ -472,7 +481,7 @@ __device__ RouteTab build_routing(const Plan& P, const int32_t* idx, const float
 __device__ RouteTab build_routing_lanes(const Plan& P, int e, float wv, uint8_t* tab, int* scratch) {
   const int S = P.S, k = P.k;
   int4* act = reinterpret_cast<int4*>(tab);
-  int* slot_tok = reinterpret_cast<int*>(act + P.max_act);
+  int* slot_tok = reinterpret_cast<int*>(act + max_records(P));
   float* slot_w = reinterpret_cast<float*>(slot_tok + S);
   int* slot_e = reinterpret_cast<int*>(slot_w + S);
   int* tok_slot = slot_e + S;
@@ -500,23 +509,25 @@ __device__ RouteTab build_routing_lanes(const Plan& P, int e, float wv, uint8_t*
     const int below = cnt & 0xFF, same = (cnt >> 8) & 0xFF, before = cnt >> 16;
     const bool valid = e >= 0;
     const int pos = min(below + before, S - 1);
-    // which slots start an expert, as a mask: the valid selections fill slots
+    // which slots start a record, as a mask: the valid selections fill slots
     // 0 .. n - 1
-    const int n = __popcll(__ballot(valid));
-    if (valid) scratch[pos] = before == 0;
+    const int n = __popcll(__ballot(valid)), rs = record_shift(P), rows = 1 << rs;
+    const bool start = valid && (before & (rows - 1)) == 0;
+    if (valid) scratch[pos] = start;
     wave_lds_sync();
-    const unsigned long long firsts = __ballot(l < n && scratch[l] != 0);
+    const unsigned long long starts = __ballot(l < n && scratch[l] != 0);
+    const int nr = (same + rows - 1) >> rs;
     if (l < S) {
       if (valid) {
         slot_tok[pos] = l / k;
         slot_w[pos] = wv;
-        slot_e[pos] = e;
+        slot_e[pos] = e | nr << 16;
       }
       tok_slot[l] = valid ? pos : -1;
-      const int a = __popcll(firsts & ((1ull << below) - 1ull));
-      if (valid && before == 0 && a < P.max_act) act[a] = make_int4(e, below, same, 0);
+      const int a = __popcll(starts & ((1ull << pos) - 1ull));
+      if (start && a < max_records(P)) act[a] = make_int4(e, pos, min(rows, same - before), nr);
     }
-    if (l == 0) s_nact = min(__popcll(firsts), P.max_act);
+    if (l == 0) s_nact = min(__popcll(starts), max_records(P));
   }
   __syncthreads();
   trace_mark(3);
@@ -1399,10 +1410,10 @@ __device__ __forceinline__ void item_z(const Plan& P, const Args& A, const Chain
 // expert tiles
 // ===========================================================================
 struct Routing {
-  int e, s0, ne;
+  int e, s0, ne, nrec;
 };
 
-// (expert, first slot, slot count) of active expert a, clamped to the valid
+// (expert, first slot, slot count, records) of record a, clamped to the valid
 // ranges so that no table content can address memory outside the layer
 __device__ __forceinline__ Routing expert_of(const Plan& P, const RouteTab& RT, int a) {
   // the record is the same in every lane: held in scalar registers, it keeps
@@ -1411,7 +1422,7 @@ __device__ __forceinline__ Routing expert_of(const Plan& P, const RouteTab& RT, 
   const int e = __builtin_amdgcn_readfirstlane(v.x), first = __builtin_amdgcn_readfirstlane(v.y);
   const int n = __builtin_amdgcn_readfirstlane(v.z);
   const int s0 = min(max(first, 0), P.S);
-  return {min(max(e, 0), P.E - 1), s0, min(max(n, 0), P.S - s0)};
+  return {min(max(e, 0), P.E - 1), s0, min(max(n, 0), P.S - s0), __builtin_amdgcn_readfirstlane(v.w)};
 }
 
 // One code book (K words of D bf16, zero words past K): thread c loads word c.
@@ -1511,7 +1522,7 @@ __device__ void item_gateup_t(const Plan& P, const Args& A, const RouteTab& RT, 
       ws.st1(ws.off(gu + (((size_t)(R.s0 + t) * 2 + pj) * P.ns + s) * I + col), acc);
     __syncthreads();
   }
-  publish(wsp<int>(A, P.o_gu_tick) + (a * P.ncg + cg) * kTickPad);
+  publish(wsp<int>(A, P.o_gu_tick) + (R.e * P.ncg + cg) * kTickPad);
 }
 
 template <int D, bool LATE, bool LINES, bool XP, int PDC>
@@ -1593,7 +1604,7 @@ __device__ __forceinline__ void item_gateup(const Plan& P, const Args& A, const 
     for (int t = 0; t < R.ne; ++t)
       store_acc(WsAccess(A, P), acc, 1, c0, I, [&](int) { return gu + (((size_t)(R.s0 + t) * 2 + pj) * P.ns + s) * I; });
     trace_mark(2);
-    publish(wsp<int>(A, P.o_gu_tick) + (a * P.ncg + cg) * kTickPad);
+    publish(wsp<int>(A, P.o_gu_tick) + (R.e * P.ncg + cg) * kTickPad);
     return;
   }
   for (int tg = 0; tg < R.ne; tg += P.nt_max) {
@@ -1661,7 +1672,7 @@ __device__ __forceinline__ void item_gateup(const Plan& P, const Args& A, const 
 
   // counts the tile done for (a, cg); the down tiles form p from the
   // n_proj ns partial sums of their columns
-  publish(wsp<int>(A, P.o_gu_tick) + (a * P.ncg + cg) * kTickPad);
+  publish(wsp<int>(A, P.o_gu_tick) + (R.e * P.ncg + cg) * kTickPad);
 }
 
 // Down tile (a, cgx, s) over split s of I, 256 output columns: for cgx <
@@ -1688,10 +1699,11 @@ __device__ __forceinline__ void down_body(const Plan& P, const Args& A, const Ro
                                           int c0, int n_out, Prime prime, Stage stage, Run run, Dst dst,
                                           uint8_t* smem) {
   prime();
-  // every gate/up tile of the column groups holding inputs [32 ks0, 32 ks1)
+  // every gate/up tile of the expert (all of its records count on one tick) on
+  // the column groups holding inputs [32 ks0, 32 ks1)
   const int cg0 = ks0 * 32 / kColsPerGroup, ncgw = (ks1 * 32 - 1) / kColsPerGroup - cg0 + 1;
-  const int* tick = wsp<const int>(A, P.o_gu_tick) + (a * P.ncg + cg0) * kTickPad;
-  wait_all(A, ncgw, [&](int i) { return ld_dev(tick + i * kTickPad) >= n_proj(P) * P.ns; });
+  const int* tick = wsp<const int>(A, P.o_gu_tick) + (R.e * P.ncg + cg0) * kTickPad;
+  wait_all(A, ncgw, [&](int i) { return ld_dev(tick + i * kTickPad) >= n_proj(P) * P.ns * R.nrec; });
   const int ld = (ks1 - ks0) * 8 + 1;
   uint4* ps = reinterpret_cast<uint4*>(smem);
   const WsAccess ws(A, P);
@@ -1716,10 +1728,11 @@ template <bool RELU2, int NACC, typename Prime, typename Stage, typename Run, ty
 __device__ __forceinline__ void down_body_wide(const Plan& P, const Args& A, const Routing& R, int a, int ks0, int ks1,
                                           Prime prime, Stage stage, Run run, Finish finish, uint8_t* smem) {
   prime();
-  // every gate/up tile of the column groups holding inputs [32 ks0, 32 ks1)
+  // every gate/up tile of the expert (all of its records count on one tick) on
+  // the column groups holding inputs [32 ks0, 32 ks1)
   const int cg0 = ks0 * 32 / kColsPerGroup, ncgw = (ks1 * 32 - 1) / kColsPerGroup - cg0 + 1;
-  const int* tick = wsp<const int>(A, P.o_gu_tick) + (a * P.ncg + cg0) * kTickPad;
-  wait_all(A, ncgw, [&](int i) { return ld_dev(tick + i * kTickPad) >= n_proj(P) * P.ns; });
+  const int* tick = wsp<const int>(A, P.o_gu_tick) + (R.e * P.ncg + cg0) * kTickPad;
+  wait_all(A, ncgw, [&](int i) { return ld_dev(tick + i * kTickPad) >= n_proj(P) * P.ns * R.nrec; });
   const int ld = (ks1 - ks0) * 8 + 1;
   uint4* ps = reinterpret_cast<uint4*>(smem);
   const WsAccess ws(A, P);
@@ -1866,7 +1879,7 @@ __device__ void item_gateup_dense(const Plan& P, const Args& A, const RouteTab& 
     store_acc(WsAccess(A, P), acc, nt, c0, I,
               [&](int t) { return gu + (((size_t)(R.s0 + tg + t) * 2 + pj) * P.ns + s) * I; });
   }
-  publish(wsp<int>(A, P.o_gu_tick) + (a * P.ncg + cg) * kTickPad);
+  publish(wsp<int>(A, P.o_gu_tick) + (R.e * P.ncg + cg) * kTickPad);
 }
 
 // Dense down tile (a, cgx, s): 256 output columns of W_down[e] [I][H] over
@@ -1949,7 +1962,8 @@ __device__ __forceinline__ void item_combine(const Plan& P, const Args& A, const
       const int c = i % ncol, tj = i / ncol;
       const int sl = s_slot[tj];
       if (sl < 0) return true;
-      return ld_dev(dnd + (s_e_slot[sl] * per_e + (c == 0 ? cgy : P.ncgh)) * kTickPad) >= (c == 0 ? nsd : P.ncgr * nsdl);
+      const int e = s_e_slot[sl] & 0xFFFF, nrec = s_e_slot[sl] >> 16;
+      return ld_dev(dnd + (e * per_e + (c == 0 ? cgy : P.ncgh)) * kTickPad) >= nrec * (c == 0 ? nsd : P.ncgr * nsdl);
     });
   }
   trace_mark(2);
@@ -2307,7 +2321,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2), minsize
                                                      lw[4] | (lw[5] << 16), lw[6] | (lw[7] << 16));
     }
   }
-  tr_route.done(A, P, P.n_pre + P.max_act * (gateup_tiles_per_expert(P) + down_tiles_per_expert(P)) + P.n_cb +
+  tr_route.done(A, P, P.n_pre + max_records(P) * (gateup_tiles_per_expert(P) + down_tiles_per_expert(P)) + P.n_cb +
                           blockIdx.x, 8);
   const int nact = RT.nact;
   const int nvq = (P.ncgh + DNW - 1) / DNW * P.nsd;  // VQ down tiles per expert

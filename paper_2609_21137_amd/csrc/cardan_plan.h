@@ -17,7 +17,7 @@
 //                   waves' sums added
 //   select          per token: logits, top-k, gating
 //   z reduce        256 outputs of z = U^T x each
-//   gate/up tiles   (active expert a, gate|up, 256 columns, split of the
+//   gate/up tiles   (record a of the active experts, gate|up, 256 columns, split of the
 //                   joint axis [H inputs | r ranks]), partial sums; the down
 //                   tiles form p = silu(g) * u from them (up-only experts: up
 //                   tiles alone, p = relu(u)^2)
@@ -103,6 +103,8 @@ enum { F_ROUTE = 1, F_Z = 2, F_GROUP = 4, F_EXPERTS = 8,
 enum { C_ERR = 0, C_SINK = 1, C_NUM };  // C_SINK: where prefetch loads are folded into one store
 constexpr int kCtrStride = 16;      // ints between counters
 constexpr int kBookShiftPos = 20;   // bits [20, 24) of the plan's flags: log2(line bytes / 16) of the book
+constexpr int kRecordShiftPos = 24; // bits [24, 28): log2 of the token rows of a routing record
+constexpr int kOneRecord = 12;      // its value for one record per expert (4096 rows, more than selections)
 constexpr int kTickPad = 32;        // ints between the tile counters (one 128-byte line each)
 
 struct Plan {
@@ -181,6 +183,17 @@ __host__ __device__ constexpr bool book_lines(int d, bool xpre) { return d != 4 
 // z items of one group of tokens: (basis, 64 ranks, four splits of H).
 __host__ __device__ inline int z_items_per_group(const Plan& P) {
   return (P.z_sep ? 2 : 1) * ((P.r + 63) / 64) * P.nq_z;
+}
+// log2 of the most token rows of one record of the routing tables: a pass of a
+// tile (rounded down to a power of two: no division in the tables), or
+// kOneRecord where an expert cannot have more tokens than a pass and where the
+// records of the passes would not fit LDS (a caller's repeats of an expert then
+// make passes within one record).
+__host__ __device__ inline int record_shift(const Plan& P) { return (P.flags >> kRecordShiftPos) & 15; }
+// Most records of a call: every active expert, and each full record.
+__host__ __device__ inline int max_records(const Plan& P) {
+  const int n = P.max_act + (P.S >> record_shift(P));
+  return n < P.S ? n : P.S;
 }
 // projections with gate/up tiles: gate and up, or up alone
 __host__ __device__ inline int n_proj(const Plan& P) { return (P.flags & F_UP_RELU2) ? 1 : 2; }

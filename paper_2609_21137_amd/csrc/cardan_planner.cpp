@@ -217,8 +217,9 @@ Plan plan_once(const cardan_shape* s, int B, int z_sep, int flags) {
     byte_splits(P, exp_act, npj, KSX, KSZ, KSD, mode);
   else
     compressed_splits(P, exp_act, npj, KSX, KSZ, KSD, mode);
-  // routing tables: active-expert records and four per-slot arrays
-  P.lds_routing = round256((size_t)P.max_act * 16 + (size_t)4 * P.S * 4);
+  // routing tables: records and four per-slot arrays (here with as many records
+  // as the fewest rows of a pass could make)
+  P.lds_routing = round256((size_t)std::min(P.S, P.max_act + P.S / 2) * 16 + (size_t)4 * P.S * 4);
   const size_t budget = by_bytes ? kLdsBudget : std::min(kLdsBudget, kLdsMax - std::min(kLdsMax, P.lds_routing));
   // Operand staging that does not fit LDS: split the codes (up to four ways)
   // before halving the token rows of a pass (down to 4), since experts with
@@ -310,7 +311,18 @@ Plan plan_once(const cardan_shape* s, int B, int z_sep, int flags) {
   P.lds_route = lds_route(P);
   // item LDS, also the grouping scratch at the start of the kernel
   const size_t group_scratch = round256((size_t)2 * P.S * 4 + (size_t)4 * P.E * 4 + 32);
-  P.lds_expert = P.lds_routing + std::max(lds_expert(P), group_scratch) + ((P.flags & F_XPRE) ? kXpreBytes : 0);
+  const size_t items = std::max(lds_expert(P), group_scratch) + ((P.flags & F_XPRE) ? kXpreBytes : 0);
+  auto routing = [&]() { return round256((size_t)max_records(P) * 16 + (size_t)4 * P.S * 4); };
+  int rs = kOneRecord;
+  if (P.nt_max < B)
+    for (rs = 0; 2 << rs <= P.nt_max;) ++rs;
+  P.flags |= rs << kRecordShiftPos;
+  P.lds_routing = routing();
+  if (P.lds_routing + items > kLdsMax) {
+    P.flags = (P.flags & ~(15 << kRecordShiftPos)) | kOneRecord << kRecordShiftPos;
+    P.lds_routing = routing();
+  }
+  P.lds_expert = P.lds_routing + items;
   // the large-batch kernel only where two workgroups with at least 64-byte
   // book lines fit a CU (80 KB each)
   constexpr size_t kLdsHalf = 80 * 1024 - 512;

@@ -148,3 +148,25 @@ def test_noalloc_smaller_layout(C):
     torch.cuda.synchronize()
     assert torch.equal(idx, idx2)
     assert float((y - y2).abs().max()) <= 2e-5 * float(y.abs().max())
+
+
+@pytest.mark.parametrize("B,k,E", ((9, 1, 2), (16, 2, 3), (17, 3, 4), (40, 5, 6), (64, 4, 5)))
+@pytest.mark.parametrize("form", ("layer", "relu2", "dense"))
+def test_experts_of_several_passes(C, form, B, k, E):
+    """Experts of 8 to 64 tokens: a record, and so tiles of their own, for every
+    8 of them, from both table builders (up to and over 64 selections)."""
+    if form != "dense":
+        _parity(C, 192, 96, E, k, 8, 256, 40, B, seed=880 + B, up_only=form == "relu2")
+        return
+    H, I = 192, 96
+    L = synth.make_layer(H, I, E, 8, 1, 0, seed=890)
+    W = synth.make_dense_weights(H, I, E, seed=890)
+    x = synth.make_input(H, B, seed=890)
+    y_ref, idx_ref, _, _ = O.moe_layer_dense(x, L["router_w"], L["router_bias"], W["W_gate"], W["W_up"],
+                                             W["W_down"], k)
+    dl = C.DenseLayer({"router_w": C.bf16_tensor(L["router_w"]), "router_bias": torch.from_numpy(L["router_bias"]).cuda(),
+                       **{n: C.bf16_tensor(W[n]) for n in ("W_gate", "W_up", "W_down")}})
+    y, idx, _ = C.dense_moe_layer(C.make_shape(H, I, E, k, 8, 1, 0), C.bf16_tensor(x), dl)
+    torch.cuda.synchronize()
+    assert np.array_equal(idx.cpu().numpy(), idx_ref)
+    assert np.abs(y.cpu().numpy() - y_ref).max() <= 4e-5 * np.abs(y_ref).max()
