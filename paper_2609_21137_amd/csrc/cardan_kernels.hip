@@ -863,8 +863,11 @@ __device__ __forceinline__ void item_z_reduce(const Plan& P, const Args& A, int 
 //     a float32 operand). With 2 sets a pass has at most 8 token rows, so one
 //     MFMA takes both parts: rows 0..7 the hi parts, rows 8..15 the lo parts
 //     of the same tokens; merge_split adds the two halves of D after the run.
-//     (Two MFMAs and two operand reads per weight operand instead: Qwen3 B=16
-//     expert kernel 39.6 us, the VQ down phase bound by LDS reads.)
+//     With kTwoProducts the two parts are two products into the same
+//     accumulators (DeepSeek-V2-Lite B=8 3.4 % slower, Qwen3 B=16 0.3 %): the
+//     stacked step's form. Its layers round each other's outputs to bf16, so
+//     the order of a sum decides roundings that grow through the stack (2e-3
+//     of y after four layers), and the step keeps the order it always had.
 //   W (weights): lane l holds rows 32 ks + 8 g .. + 8 of output column
 //     c0 + 4 n + q for MFMA q = 0..3. For VQ weights this slice is one code
 //     word (d = 8) or two (d = 4) read from the LDS code book; for dense bf16
@@ -878,19 +881,25 @@ __device__ __forceinline__ void item_z_reduce(const Plan& P, const Args& A, int 
 // (never stored) instead of branching around the LDS read.
 __device__ __forceinline__ int a_row(int n, int nt) { return min(n, nt - 1); }
 
+// NOPS of a split operand whose parts are two products.
+constexpr int kTwoProducts = 3;
+
 // LDS operand index of lane l at K-step `step` (relative to the staged rows)
-// for NOPS sets: the token row's group, of the lo part in rows 8..15 with two.
+// for NOPS sets: the token row's group, of the lo part in rows 8..15 with two
+// (with two products the hi part, the lo part following it).
 template <int NOPS>
 __device__ __forceinline__ int a_index(int l, int nt, int ld, int step) {
   const int n = l & 15, g = l >> 4;
   if constexpr (NOPS == 1) return a_row(n, nt) * ld + step * 4 + g;
+  if constexpr (NOPS == kTwoProducts) return a_row(n, nt) * ld + (step * 4 + g) * 2;
   return a_row(n & 7, nt) * ld + (step * 4 + g) * 2 + (n >> 3);
 }
 
 // Adds the two halves of D of a split operand's products: row t (hi) and row
 // t + 8 (lo) sit 32 lanes apart.
-template <int N>
+template <int SP, int N>
 __device__ __forceinline__ void merge_split(f32x4* acc) {
+  if constexpr (SP == kTwoProducts) return;
 #pragma unroll
   for (int q = 0; q < N; ++q)
 #pragma unroll
@@ -1009,13 +1018,20 @@ struct VqPipe {
                                        const uint4* __restrict__ ops, int ops_ld, int ops_ks0, int nt,
                                        f32x4 acc[4]) {
     const int l = threadIdx.x & 63;
-    const uint4 a0 = ops[a_index<NOPS>(l, nt, ops_ld, ks - ops_ks0)];
+    const int oi = a_index<NOPS>(l, nt, ops_ld, ks - ops_ks0);
+    const uint4 a0 = ops[oi];
+    uint4 a1 = a0;
+    if constexpr (NOPS == kTwoProducts) a1 = ops[oi + 1];
     uint4 w[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) w[q] = cb.word(b, q);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) acc[q] = mfma_bf16(a0, w[q], acc[q]);
-    sched_step<1 + 4 * W, 4>();
+    for (int q = 0; q < 4; ++q) {
+      acc[q] = mfma_bf16(a0, w[q], acc[q]);
+      if constexpr (NOPS == kTwoProducts) acc[q] = mfma_bf16(a1, w[q], acc[q]);
+    }
+    constexpr int T = NOPS == kTwoProducts ? 2 : 1;
+    sched_step<T + 4 * W, 4 * T>();
   }
   __device__ __forceinline__ void run(const BookView<D, LINES>& cb, const uint4* ops, int ops_ld, int ops_ks0,
                                       int nt, f32x4 acc[4]) {
@@ -1054,7 +1070,7 @@ struct VqPipe {
 // of two column groups, float32 activations as bf16 hi + lo): each K-step's
 // activation reads serve both sub-tiles. A second sub-tile past n_out reads
 // zeros (its results are never stored).
-template <int D, int PD, bool LINES>
+template <int D, int NOPS, int PD, bool LINES>
 struct VqPipe2 {
   static constexpr int W = D == 8 ? 1 : 2;
   uint32_t buf[PD][2 * W];
@@ -1090,7 +1106,10 @@ struct VqPipe2 {
   __device__ __forceinline__ void step(int ks, const uint32_t (&b)[2 * W], const BookView<D, LINES>& cb,
                                        const uint4* __restrict__ ops, int ops_ld, int ops_ks0, int nt,
                                        f32x4 acc[8]) {
-    const uint4 a0 = ops[a_index<2>(threadIdx.x & 63, nt, ops_ld, ks - ops_ks0)];
+    const int oi = a_index<NOPS>(threadIdx.x & 63, nt, ops_ld, ks - ops_ks0);
+    const uint4 a0 = ops[oi];
+    uint4 a1 = a0;
+    if constexpr (NOPS == kTwoProducts) a1 = ops[oi + 1];
     uint4 w[8];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -1098,8 +1117,12 @@ struct VqPipe2 {
       w[4 + q] = cb.word(b + W, q);
     }
 #pragma unroll
-    for (int q = 0; q < 8; ++q) acc[q] = mfma_bf16(a0, w[q], acc[q]);
-    sched_step<1 + (D == 8 ? 8 : 16), 8>();
+    for (int q = 0; q < 8; ++q) {
+      acc[q] = mfma_bf16(a0, w[q], acc[q]);
+      if constexpr (NOPS == kTwoProducts) acc[q] = mfma_bf16(a1, w[q], acc[q]);
+    }
+    constexpr int T = NOPS == kTwoProducts ? 2 : 1;
+    sched_step<T + (D == 8 ? 8 : 16), 8 * T>();
   }
   __device__ __forceinline__ void run(const BookView<D, LINES>& cb, const uint4* ops, int ops_ld, int ops_ks0, int nt,
                                       f32x4 acc[8]) {
@@ -1165,13 +1188,23 @@ struct DensePipe {
   }
   __device__ __forceinline__ void step(int ks, const uint2 (&b)[8], const uint4* __restrict__ ops, int ops_ld,
                                        int ops_ks0, int nt, f32x4 acc[4]) {
-    const uint4 a0 = ops[a_index<NOPS>(threadIdx.x & 63, nt, ops_ld, ks - ops_ks0)];
+    const int oi = a_index<NOPS>(threadIdx.x & 63, nt, ops_ld, ks - ops_ks0);
+    const uint4 a0 = ops[oi];
+    uint4 a1 = a0;
+    if constexpr (NOPS == kTwoProducts) a1 = ops[oi + 1];
     const uint4 w0 = dense_w<0>(b), w1 = dense_w<1>(b), w2 = dense_w<2>(b), w3 = dense_w<3>(b);
     acc[0] = mfma_bf16(a0, w0, acc[0]);
     acc[1] = mfma_bf16(a0, w1, acc[1]);
     acc[2] = mfma_bf16(a0, w2, acc[2]);
     acc[3] = mfma_bf16(a0, w3, acc[3]);
-    sched_step<1, 4>();
+    if constexpr (NOPS == kTwoProducts) {
+      acc[0] = mfma_bf16(a1, w0, acc[0]);
+      acc[1] = mfma_bf16(a1, w1, acc[1]);
+      acc[2] = mfma_bf16(a1, w2, acc[2]);
+      acc[3] = mfma_bf16(a1, w3, acc[3]);
+    }
+    constexpr int T = NOPS == kTwoProducts ? 2 : 1;
+    sched_step<T, 4 * T>();
   }
   __device__ __forceinline__ void run(const uint4* ops, int ops_ld, int ops_ks0, int nt, f32x4 acc[4]) {
     if (nks <= PD) {  // every step was primed: no refills
@@ -1200,14 +1233,18 @@ __device__ __forceinline__ void zero_acc(f32x4 acc[4]) {
 
 // acc += the products of a split operand (their halves of D merged first:
 // rows 8..15 of acc may hold repeats of a token row).
-template <int PD>
-__device__ __forceinline__ void run_split(DensePipe<2, PD>& pipe, const uint4* ops, int ld, int ks0, int nt,
+template <int SP, int PD>
+__device__ __forceinline__ void run_split(DensePipe<SP, PD>& pipe, const uint4* ops, int ld, int ks0, int nt,
                                           f32x4 acc[4]) {
+  if constexpr (SP == kTwoProducts) {
+    pipe.run(ops, ld, ks0, nt, acc);
+    return;
+  }
   if (pipe.nks <= 0) return;
   f32x4 part[4];
   zero_acc(part);
   pipe.run(ops, ld, ks0, nt, part);
-  merge_split<4>(part);
+  merge_split<SP, 4>(part);
 #pragma unroll
   for (int q = 0; q < 4; ++q) acc[q] += part[q];
 }
@@ -1525,7 +1562,7 @@ __device__ void item_gateup_t(const Plan& P, const Args& A, const RouteTab& RT, 
   publish(wsp<int>(A, P.o_gu_tick) + (R.e * P.ncg + cg) * kTickPad);
 }
 
-template <int D, bool LATE, bool LINES, bool XP, int PDC>
+template <int D, bool LATE, bool LINES, bool XP, int SP, int PDC>
 __device__ __forceinline__ void item_gateup(const Plan& P, const Args& A, const RouteTab& RT, int a, int pj, int cg, int s,
                             bool lr_first, uint4* cbs, uint8_t* smem, const uint4* xpre, const uint4* zpre) {
   const Routing R = expert_of(P, RT, a);
@@ -1548,7 +1585,7 @@ __device__ __forceinline__ void item_gateup(const Plan& P, const Args& A, const 
   const float* zsrc = (P.flags & F_Z) ? A.z_out : A.z_in;
 
   VqPipe<D, 1, PDC, LINES> vq;
-  DensePipe<2, kPdDense> lr;
+  DensePipe<SP, kPdDense> lr;
   const BookView<D, LINES> cb(cbs, book_shift(P));
   const int n8x = (x1 - x0) * 4, n8z = (z1 - z0) * 4;  // 8-element groups per token row
   // Activation loads through buffer resources over x [B][H] and z [2][B][r]
@@ -1694,7 +1731,7 @@ __device__ __forceinline__ void stage_p_ns(const WsAccess& ws, const Plan& P, ui
     stage_p<1, 8, RELU2>(ws, P, ps, ld, nt, nquad, slot0, col0);
 }
 
-template <bool RELU2, typename Prime, typename Stage, typename Run, typename Dst>
+template <bool RELU2, int SP, typename Prime, typename Stage, typename Run, typename Dst>
 __device__ __forceinline__ void down_body(const Plan& P, const Args& A, const Routing& R, int a, int ks0, int ks1,
                                           int c0, int n_out, Prime prime, Stage stage, Run run, Dst dst,
                                           uint8_t* smem) {
@@ -1719,12 +1756,12 @@ __device__ __forceinline__ void down_body(const Plan& P, const Args& A, const Ro
     f32x4 acc[4];
     zero_acc(acc);
     run(ps, ld, nt, acc);
-    merge_split<4>(acc);
+    merge_split<SP, 4>(acc);
     store_acc(ws, acc, nt, c0, n_out, [&](int t) { return dst(R.s0 + tg + t); });
   }
 }
 
-template <bool RELU2, int NACC, typename Prime, typename Stage, typename Run, typename Finish>
+template <bool RELU2, int SP, int NACC, typename Prime, typename Stage, typename Run, typename Finish>
 __device__ __forceinline__ void down_body_wide(const Plan& P, const Args& A, const Routing& R, int a, int ks0, int ks1,
                                           Prime prime, Stage stage, Run run, Finish finish, uint8_t* smem) {
   prime();
@@ -1749,12 +1786,12 @@ __device__ __forceinline__ void down_body_wide(const Plan& P, const Args& A, con
 #pragma unroll
     for (int q = 0; q < NACC; q += 4) zero_acc(acc + q);
     run(ps, ld, nt, acc);
-    merge_split<NACC>(acc);
+    merge_split<SP, NACC>(acc);
     finish(ws, acc, nt, R.s0 + tg);
   }
 }
 
-template <int D, bool LINES, bool RELU2>
+template <int D, bool LINES, int SP, bool RELU2>
 __device__ void item_down_vq(const Plan& P, const Args& A, const RouteTab& RT, int a, int cgx, int s,
                              uint4* cbs, uint8_t* smem) {
   const Routing R = expert_of(P, RT, a);
@@ -1764,9 +1801,9 @@ __device__ void item_down_vq(const Plan& P, const Args& A, const RouteTab& RT, i
   const uint8_t* codes = A.L.codes_down + (size_t)R.e * (I / D) * H;
   float* dn = wsp<float>(A, P.o_dn) + (size_t)s * S * H;
   // d = 2 holds four code rows per K-step: half the steps in flight (same registers as d = 4)
-  VqPipe<D, 2, D == 2 ? kPdVq / 2 : kPdVq, LINES> pipe;
+  VqPipe<D, SP, D == 2 ? kPdVq / 2 : kPdVq, LINES> pipe;
   uint4 bk;
-  down_body<RELU2>(P, A, R, a, ks0, ks1, c0, H,
+  down_body<RELU2, SP>(P, A, R, a, ks0, ks1, c0, H,
             [&]() {
               bk = book_load<D>(A.L.cb_down, P.K);
               __builtin_amdgcn_sched_barrier(0);
@@ -1780,7 +1817,7 @@ __device__ void item_down_vq(const Plan& P, const Args& A, const RouteTab& RT, i
 
 // VQ down tile over two column groups (cgx, cgx + 1): as item_down_vq, each
 // wave on 64 columns of both groups.
-template <int D, bool LINES, bool RELU2>
+template <int D, bool LINES, int SP, bool RELU2>
 __device__ void item_down_vq2(const Plan& P, const Args& A, const RouteTab& RT, int a, int cgx, int s,
                               uint4* cbs, uint8_t* smem) {
   const Routing R = expert_of(P, RT, a);
@@ -1789,9 +1826,9 @@ __device__ void item_down_vq2(const Plan& P, const Args& A, const RouteTab& RT, 
   const int c0 = cgx * kColsPerGroup + (threadIdx.x >> 6) * 64;
   const uint8_t* codes = A.L.codes_down + (size_t)R.e * (I / D) * H;
   float* dn = wsp<float>(A, P.o_dn) + (size_t)s * S * H;
-  VqPipe2<D, kPdVqWide, LINES> pipe;
+  VqPipe2<D, SP, kPdVqWide, LINES> pipe;
   uint4 bk;
-  down_body_wide<RELU2, 8>(P, A, R, a, ks0, ks1,
+  down_body_wide<RELU2, SP, 8>(P, A, R, a, ks0, ks1,
                [&]() {
                  bk = book_load<D>(A.L.cb_down, P.K);
                  __builtin_amdgcn_sched_barrier(0);
@@ -1817,7 +1854,7 @@ __device__ void item_down_vq2(const Plan& P, const Args& A, const RouteTab& RT, 
 // Low-rank down tile (a, cgr, s): partial A_e^T p over split s of I. The
 // last of the expert's ncgr * nsdl tiles sums the splits into u_e[slot]
 // (r values per slot) and flags the expert's low-rank part done.
-template <bool RELU2>
+template <int SP, bool RELU2>
 __device__ void item_down_lr(const Plan& P, const Args& A, const RouteTab& RT, int a, int cgr, int s,
                              uint8_t* smem) {
   const Routing R = expert_of(P, RT, a);
@@ -1826,8 +1863,8 @@ __device__ void item_down_lr(const Plan& P, const Args& A, const RouteTab& RT, i
   const int c0 = cgr * kColsPerGroup + (threadIdx.x >> 6) * 64;
   const uint16_t* Ae = A.L.A_down + (size_t)R.e * I * r;
   float* uap = wsp<float>(A, P.o_uap);
-  DensePipe<2, kPdDense> pipe;
-  down_body<RELU2>(P, A, R, a, ks0, ks1, c0, r, [&]() { pipe.prime(Ae, r, c0, r, I, ks0, ks1); }, [&]() {},
+  DensePipe<SP, kPdDense> pipe;
+  down_body<RELU2, SP>(P, A, R, a, ks0, ks1, c0, r, [&]() { pipe.prime(Ae, r, c0, r, I, ks0, ks1); }, [&]() {},
             [&](const uint4* ps, int ld, int nt, f32x4* acc) { pipe.run(ps, ld, ks0, nt, acc); },
             [&](int slot) { return uap + ((size_t)s * S + slot) * r; }, smem);
   // the combine sums the nsdl partials of u_e itself
@@ -1894,7 +1931,7 @@ __device__ void item_down_dense(const Plan& P, const Args& A, const RouteTab& RT
   const uint16_t* W = reinterpret_cast<const uint16_t*>(A.L.codes_down) + (size_t)R.e * I * H;
   float* dn = wsp<float>(A, P.o_dn) + (size_t)s * S * H;
   DensePipe<2, kPdDenseW> pipe;
-  down_body<RELU2>(P, A, R, a, ks0, ks1, c0, H, [&]() { pipe.prime(W, H, c0, H, I, ks0, ks1); }, [&]() {},
+  down_body<RELU2, 2>(P, A, R, a, ks0, ks1, c0, H, [&]() { pipe.prime(W, H, c0, H, I, ks0, ks1); }, [&]() {},
             [&](const uint4* ps, int ld, int nt, f32x4* acc) { pipe.run(ps, ld, ks0, nt, acc); },
             [&](int slot) { return dn + (size_t)slot * H; }, smem);
   publish(wsp<int>(A, P.o_dn_done) + (R.e * (P.ncgh + 1) + cgx) * kTickPad);
@@ -1909,7 +1946,7 @@ __device__ void item_down_dense(const Plan& P, const Args& A, const RouteTab& RT
 // SK (large r, small batches): the tile covers 64 columns and its four waves
 // split the ranks of B^T u, so each wave's share of B fits its prime before
 // the wait; the waves' accumulators are summed through LDS.
-template <bool LRD, bool SK>
+template <bool LRD, bool SK, int SP>
 __device__ __forceinline__ void item_combine(const Plan& P, const Args& A, const Chain& C, const RouteTab& RT, int jc,
                              uint8_t* smem) {
   constexpr int NQ4 = SK ? 4 : 1;  // tiles per 256-column group
@@ -1924,7 +1961,7 @@ __device__ __forceinline__ void item_combine(const Plan& P, const Args& A, const
   // B is primed in full for r <= 128 (later K-steps load during the run);
   // SK: wave w primes K-steps [w KSR / 4, (w + 1) KSR / 4) of the tile's columns
   const int bk0 = SK ? w * KSR / 4 : 0, bk1 = SK ? (w + 1) * KSR / 4 : KSR;
-  DensePipe<2, 4> bp;
+  DensePipe<SP, 4> bp;
   if (r > 0) bp.prime(A.L.B_down, H, cbase + (SK ? 0 : w * 64), H, r, bk0, bk1);
 
   const int* s_slot = RT.tok_slot + t0 * k;  // (t, j) -> slot of the tile's tokens
@@ -2029,7 +2066,7 @@ __device__ __forceinline__ void item_combine(const Plan& P, const Args& A, const
     f32x4 acc[4];
     zero_acc(acc);
     bp.run(us, ld, 0, nt, acc);
-    merge_split<4>(acc);
+    merge_split<SP, 4>(acc);
     float* red4 = reinterpret_cast<float*>(smem + combine_lds(P));  // [4 waves][64 lanes][16]
     const int l = tid & 63;
 #pragma unroll
@@ -2055,7 +2092,7 @@ __device__ __forceinline__ void item_combine(const Plan& P, const Args& A, const
     f32x4 acc[4];
     zero_acc(acc);
     bp.run(us, ld, 0, nt, acc);
-    merge_split<4>(acc);
+    merge_split<SP, 4>(acc);
     trace_mark(1);
     const int l = tid & 63, n = l & 15, g = l >> 4;
     const int c = w * 64 + 4 * n;
@@ -2242,8 +2279,8 @@ __global__ __launch_bounds__(kWG) void k_route_reset(Plan P, Args A) {
 // CSK: combine tiles split over the ranks of B^T u (large r, small batches).
 // XPRE (batch 1): the token's x and z rows are loaded at kernel start, while
 // the routing tables build, into an LDS area at the end of dynamic LDS.
-// VAR: kVarRelu2 (up-only squared-ReLU experts) and kVarTBook (projection-
-// code-book gate/up tiles) bits, each a separate instantiation so that the
+// VAR: kVarRelu2 (up-only squared-ReLU experts), kVarTBook (projection-code-
+// book gate/up tiles) and kVarTwoProducts (the stacked step's sums) bits, each a separate instantiation so that the
 // gated code-word kernels carry no code of either.
 // Compiled for size (minsize): the explicitly unrolled pipelines keep their
 // unrolling, the rest of each instantiation (about 100 KB of machine code)
@@ -2253,6 +2290,7 @@ template <int D, int DNW, int MODE, bool CSK, bool XPRE, int VAR>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2), minsize)) void k_expert(Plan P, Args A,
                                                                                                Chain C) {
   constexpr bool RELU2 = (VAR & kVarRelu2) != 0, TBOOK = (VAR & kVarTBook) != 0;
+  constexpr int SP = (VAR & kVarTwoProducts) ? kTwoProducts : 2;
   constexpr bool LINES = book_lines(D, XPRE);
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   // the code book of the current item (BookView) at the start of dynamic LDS:
@@ -2360,10 +2398,10 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2), minsize
       constexpr int PDC = DNW == 2 ? kPdGateUpWide : kPdGateUp;
       if constexpr (XPRE) {
         const KernArgs& K = kern_args();
-        item_gateup<D, DNW == 2, LINES, XPRE, PDC>(K.P, K.A, RT, t.a, t.pj, t.cg, t.s, lr_first, cbs, item_smem,
+        item_gateup<D, DNW == 2, LINES, XPRE, SP, PDC>(K.P, K.A, RT, t.a, t.pj, t.cg, t.s, lr_first, cbs, item_smem,
                                                    xpre, zpre);
       } else {
-        item_gateup<D, DNW == 2, LINES, XPRE, PDC>(P, A, RT, t.a, t.pj, t.cg, t.s, lr_first, cbs, item_smem, xpre,
+        item_gateup<D, DNW == 2, LINES, XPRE, SP, PDC>(P, A, RT, t.a, t.pj, t.cg, t.s, lr_first, cbs, item_smem, xpre,
                                                    zpre);
       }
     }
@@ -2377,12 +2415,12 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2), minsize
       if constexpr (MODE != 0)
         item_down_dense<RELU2>(P, A, RT, a, rem / P.nsd, rem % P.nsd, item_smem);
       else if constexpr (DNW == 2)
-        item_down_vq2<D, LINES, RELU2>(P, A, RT, a, rem / P.nsd * 2, rem % P.nsd, cbs, item_smem);
+        item_down_vq2<D, LINES, SP, RELU2>(P, A, RT, a, rem / P.nsd * 2, rem % P.nsd, cbs, item_smem);
       else
-        item_down_vq<D, LINES, RELU2>(P, A, RT, a, rem / P.nsd, rem % P.nsd, cbs, item_smem);
+        item_down_vq<D, LINES, SP, RELU2>(P, A, RT, a, rem / P.nsd, rem % P.nsd, cbs, item_smem);
       tr.done(A, P, P.n_pre + jp, 5);
     } else {
-      item_down_lr<RELU2>(P, A, RT, a, (rem - nvq) / P.nsdl, (rem - nvq) % P.nsdl, item_smem);
+      item_down_lr<SP, RELU2>(P, A, RT, a, (rem - nvq) / P.nsdl, (rem - nvq) % P.nsdl, item_smem);
       tr.done(A, P, P.n_pre + jp, 6);
     }
   }
@@ -2390,10 +2428,10 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2), minsize
     __syncthreads();
     ItemTrace tr;
     if constexpr (XPRE) {
-      item_combine<MODE == 0, CSK>(P, A, C, RT, jp - n_gu - n_dn, item_smem);
+      item_combine<MODE == 0, CSK, SP>(P, A, C, RT, jp - n_gu - n_dn, item_smem);
     } else {
       const KernArgs& K = kern_args();
-      item_combine<MODE == 0, CSK>(K.P, K.A, K.C, RT, jp - n_gu - n_dn, item_smem);
+      item_combine<MODE == 0, CSK, SP>(K.P, K.A, K.C, RT, jp - n_gu - n_dn, item_smem);
     }
     tr.done(A, P, P.n_pre + jp, 7);
   }
@@ -2491,6 +2529,9 @@ const void* expert_kernel(const Plan& P) {
   if (mode == 1)
     return d == 8 ? kx<8, 1, 1, false, false, 0>() : d == 4 ? kx<4, 1, 1, false, false, 0>()
                                                              : kx<2, 1, 1, false, false, 0>();
+  if (P.flags & (F_NORM_IN | F_SSQ_OUT))  // the stacked step: gated code-word experts
+    return d == 8 && dn_width(P) == 2 ? kx<8, 2, 0, false, false, kVarTwoProducts>()
+                                      : kx_by_d<kVarTwoProducts>(d, csk, xpre);
   if (d == 8 && dn_width(P) == 2) return relu2 ? kx<8, 2, 0, false, false, kVarRelu2>() : kx<8, 2, 0, false, false, 0>();
   if (tb && d != 2) {
     constexpr int T = kVarTBook, TR = kVarTBook | kVarRelu2;

@@ -104,7 +104,7 @@ void compressed_splits(Plan& P, double exp_act, double npj, int KSX, int KSZ, in
   }
 }
 
-// Splits by bytes, for the all-dense layer and for F_BYTE_SPLITS: the expected
+// Splits by bytes, for the all-dense layer, the stacked step and F_BYTE_SPLITS: the expected
 // active experts' weight bytes spread over the nominal grid, kept between 16
 // and 128 KB per tile, so small batches run every tile in one round and large
 // ones stream long tiles (a VQ down K-step counts double). Dense tiles grow to
@@ -212,7 +212,8 @@ Plan plan_once(const cardan_shape* s, int B, int z_sep, int flags) {
   P.ncgh = ceil_div(P.H, kColsPerGroup);
   P.ncgr = mode == 0 ? ceil_div(P.r, kColsPerGroup) : 0;  // low-rank down column groups
   P.nsdl = 1;
-  const bool by_bytes = mode == 2 || (P.flags & F_BYTE_SPLITS);
+  // (the stacked step keeps the order of its sums: see kTwoProducts)
+  const bool by_bytes = mode == 2 || (P.flags & (F_BYTE_SPLITS | F_NORM_IN | F_SSQ_OUT));
   if (by_bytes)
     byte_splits(P, exp_act, npj, KSX, KSZ, KSD, mode);
   else
