@@ -17,7 +17,7 @@
 //                   waves' sums added
 //   select          per token: logits, top-k, gating
 //   z reduce        256 outputs of z = U^T x each
-//   gate/up tiles   (record a of the active experts, gate|up, 256 columns, split of the
+//   gate/up tiles   (record a of the routing tables, gate|up, 256 columns, split of the
 //                   joint axis [H inputs | r ranks]), partial sums; the down
 //                   tiles form p = silu(g) * u from them (up-only experts: up
 //                   tiles alone, p = relu(u)^2)

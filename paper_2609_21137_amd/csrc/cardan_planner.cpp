@@ -193,10 +193,10 @@ Plan plan_once(const cardan_shape* s, int B, int z_sep, int flags) {
   P.nch_r = ceil_div(P.H, kRowsRouter);
   P.n_eg = ceil_div(P.E, 64);
   P.z_sep = z_sep;
-  // token rows a tile stages per pass: 8 above batch 8 (an expert with more
-  // tokens streams its weights again per pass, rare at these batches), which
-  // keeps the large-batch kernel's operand staging small enough for its
-  // code book copies
+  // token rows a tile stages per pass: 8 above batch 8 (the hi and lo halves of
+  // a split operand fill one MFMA's 16 rows), which also keeps the operand
+  // staging small enough for the code book's lines; an expert with more tokens
+  // has a record, and tiles, per pass
   P.nt_max = B > 8 ? 8 : B;
   // combine tiles of few tokens, so that the final gather is spread over more
   // workgroups: B/32 each (OLMoE B=32 1 token instead of 2: 2 us less), and up
