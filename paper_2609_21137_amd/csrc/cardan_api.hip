@@ -108,13 +108,15 @@ int gateup_form(const cardan_shape*, int) {
   return 0;
 }
 
-int check_ws(const Plan& P, const void* ws, size_t ws_bytes) {
+int check_ws(size_t need, const void* ws, size_t ws_bytes) {
   if (!ws) return fail(CARDAN_ERR_NULL_PTR, "workspace is NULL");
   if (misaligned(ws)) return fail(CARDAN_ERR_ALIGN, "workspace is not 16-byte aligned");
-  if (ws_bytes < P.total)
-    return fail(CARDAN_ERR_WORKSPACE, "workspace of %zu bytes < required %zu", ws_bytes, P.total);
+  if (ws_bytes < need)
+    return fail(CARDAN_ERR_WORKSPACE, "workspace of %zu bytes < required %zu", ws_bytes, need);
   return CARDAN_OK;
 }
+
+int check_ws(const Plan& P, const void* ws, size_t ws_bytes) { return check_ws(P.total, ws, ws_bytes); }
 
 // Stacked decode step: buffers after the layer's workspace layout: y and the
 // partial sums of squares of two layers (ping-pong), and two normalised bf16
@@ -498,12 +500,14 @@ int cardan_moe_decode_step(const cardan_shape* shape, int32_t B, int32_t n_layer
       return fail(rc, "%s", msg);
     }
   const int base = F_ROUTE | F_GROUP | F_EXPERTS | (shape->r > 0 ? F_Z : 0);
-  // every layer's plan has this layout (flags and bases change item counts only)
+  // Layers that chain to a neighbour all have this layout (the side they chain
+  // on and their bases change item counts only). A stack of one layer chains to
+  // none: it runs with the single layer's layout, which can be the larger one.
   const Plan P0 = make_plan(shape, B, 1, base | F_NORM_IN | F_SSQ_OUT);
   const StepBufs sb = step_bufs(P0);
-  if ((rc = check_ws(P0, ws, ws_bytes))) return rc;
-  if (ws_bytes < sb.total)
-    return fail(CARDAN_ERR_WORKSPACE, "workspace of %zu bytes < required %zu", ws_bytes, sb.total);
+  size_t need = sb.total;
+  if (n_layers == 1) need = std::max(need, make_plan(shape, B, 1, base).total);
+  if ((rc = check_ws(need, ws, ws_bytes))) return rc;
   uint8_t* w = static_cast<uint8_t*>(ws);
   float* ybuf[2] = {reinterpret_cast<float*>(w + sb.o_y), reinterpret_cast<float*>(w + sb.o_y) + (size_t)B * shape->H};
   float* ssq[2] = {reinterpret_cast<float*>(w + sb.o_ssq),

@@ -14,7 +14,9 @@
 //     (active expert, gate|up, column group, split) for several grid sizes,
 //     and a position takes a code split exactly when its split index is
 //     below ns_v;
-//   - sizes that must fit 32-bit offsets do.
+//   - sizes that must fit 32-bit offsets do;
+//   - the layers of a stack share one layout, whichever neighbours they chain
+//     to and whatever their bases.
 #include <stdio.h>
 #include <stdlib.h>
 
@@ -41,6 +43,20 @@ static int cdiv(int a, int b) { return (a + b - 1) / b; }
 struct Counters {
   size_t rc, zc, gu, dn, rl;
 };
+
+// the first, a middle and the last layer of a stack: the step checks and lays
+// out its workspace with the middle one's plan
+static void check_step_layout(const cardan_shape& s, int B) {
+  const int all = F_ROUTE | F_Z | F_GROUP | F_EXPERTS;
+  const Plan P = make_plan(&s, B, 1, all | F_NORM_IN | F_SSQ_OUT);
+  for (int z_sep = 0; z_sep < 2; ++z_sep)
+    for (int chain : {(int)F_SSQ_OUT, (int)F_NORM_IN, F_NORM_IN | F_SSQ_OUT, F_NORM_IN | F_SSQ_OUT | F_PREFETCH}) {
+      const Plan Q = make_plan(&s, B, z_sep, (s.r > 0 ? all : all & ~F_Z) | chain);
+      snprintf(g_ctx, sizeof g_ctx, "H=%d I=%d E=%d k=%d d=%d K=%d r=%d B=%d z_sep=%d chain=%d", s.H, s.I, s.E,
+               s.top_k, s.d, s.K, s.r, B, z_sep, chain);
+      CHECK(Q.total == P.total && Q.o_z == P.o_z && combine_col_tiles(Q) == combine_col_tiles(P));
+    }
+}
 
 static void check_plan(const cardan_shape& s, int B, int z_sep, int flags, Counters* ref) {
   const Plan P = make_plan(&s, B, z_sep, flags);
@@ -182,6 +198,7 @@ int main(int argc, char** argv) {
       // projection-code-book gate/up tiles (gated and up-only)
       check_plan(s, B, 0, all | F_TBOOK, &ref);
       check_plan(s, B, 1, all | F_TBOOK | F_UP_RELU2, &ref);
+      check_step_layout(s, B);
       plans += 9;
     }
   }

@@ -223,6 +223,41 @@ def test_dense_entry_points_validation(C):
                                     FAKE, need, None) == -3
 
 
+def _required(C, rc):
+    """Bytes that a workspace refusal asks for."""
+    assert rc == -4, (rc, C.lib().cardan_last_error())
+    return int(re.search(rb"required (\d+)", C.lib().cardan_last_error()).group(1))
+
+
+STEP_SHAPES = [
+    ((2048, 768, 128, 8, 8, 256, 128), 1),    # the layer's layout is 90 KB larger than the stacked one
+    ((2048, 1408, 64, 6, 8, 256, 384), 1),
+    ((4928, 3520, 300, 20, 8, 256, 56), 34),  # 115 MB against 76
+    ((2048, 768, 128, 8, 8, 256, 128), 16),
+    ((64, 32, 1, 1, 2, 1, 0), 1),
+]
+
+
+@pytest.mark.parametrize("dims,B", STEP_SHAPES)
+def test_decode_step_asks_for_every_layout_it_runs(C, dims, B):
+    """A step of one layer runs with the single layer's layout: a workspace one
+    byte short of that is refused (each size below is, so nothing launches)."""
+    L = C.lib()
+    s = C.make_shape(*dims)
+    stack = (C.LayerStruct * 2)(_layer(C), _layer(C))
+
+    def step(n, nbytes):
+        return L.cardan_moe_decode_step(ctypes.byref(s), B, n, FAKE, stack, 1e-6, FAKE, None, FAKE, FAKE, FAKE,
+                                        nbytes, None)
+
+    layer = _required(C, L.cardan_moe_layer(ctypes.byref(s), B, FAKE, ctypes.byref(stack[0]), FAKE, FAKE, FAKE,
+                                            FAKE, 0, None))
+    one, two = _required(C, step(1, 0)), _required(C, step(2, 0))
+    assert layer <= one and two <= one
+    assert _required(C, step(1, one - 1)) == one and _required(C, step(2, two - 1)) == two
+    assert one <= _ws(C, s, B)[1]
+
+
 def test_workspace_covers_dense_forms(C):
     """The workspace size is the maximum over the compressed, dense-down and
     uncompressed layouts, whatever d, K and r the size query names."""
