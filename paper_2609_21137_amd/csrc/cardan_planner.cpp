@@ -171,8 +171,8 @@ size_t lds_route(const Plan& P) {
 size_t lds_expert(const Plan& P) {
   const int KSX = P.H / 32, KSZ = ceil_div(P.r, 32), KSD = P.I / 32;
   size_t need = (size_t)P.nt_max * gateup_ld(KSX, KSZ, P.ns, P.ns_v) * 16;
-  // down: p operand rows
-  const int ksd = std::max(ks_max(KSD, P.nsd), ks_max(KSD, P.nsdl));
+  // down: p operand rows (of the low-rank tiles where the call has them)
+  const int ksd = std::max(ks_max(KSD, P.nsd), P.ncgr > 0 ? ks_max(KSD, P.nsdl) : 0);
   need = std::max(need, (size_t)P.nt_max * (ksd * 8 + 1) * 16);
   need = std::max(need, combine_lds(P) + ((P.flags & F_CB_SPLITK) ? kSplitKRed : 0));
   // T-path gate/up tiles: the T rows of their blocks for one token
@@ -259,11 +259,13 @@ Plan plan_once(const cardan_shape* s, int B, int z_sep, int flags) {
     P.ns_v = std::min(KSX, std::max(P.ns_v, ceil_div(KSX, ks_t)));
     P.ns = P.ns_v + nl;
   }
+  // (the splits by bytes leave 8 KB more free: fewer splits would change the
+  // order of the stacked step's sums and the layers the scratch array takes)
   auto down_fits = [&](int n) {
-    return (size_t)P.nt_max * (ks_max(KSD, n) * 8 + 1) * 16 + kWG * 2 * 16 <= budget;
+    return (size_t)P.nt_max * (ks_max(KSD, n) * 8 + 1) * 16 + (by_bytes ? 8192 : 0) <= budget;
   };
   while (P.nsd < KSD && !down_fits(P.nsd)) ++P.nsd;
-  while (P.nsdl < KSD && !down_fits(P.nsdl)) ++P.nsdl;
+  while (P.ncgr > 0 && P.nsdl < KSD && !down_fits(P.nsdl)) ++P.nsdl;
   // Items for more than two rounds of the nominal grid (throughput-bound):
   // VQ down tiles over two column groups, so that each K-step's activation
   // reads serve twice the columns and the down tiles take half the

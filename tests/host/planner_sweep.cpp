@@ -14,12 +14,15 @@
 //     (active expert, gate|up, column group, split) for several grid sizes,
 //     and a position takes a code split exactly when its split index is
 //     below ns_v;
+//   - the item LDS of the expert kernel holds the largest item that the call
+//     has, and no more than that;
 //   - sizes that must fit 32-bit offsets do;
 //   - the layers of a stack share one layout, whichever neighbours they chain
 //     to and whatever their bases.
 #include <stdio.h>
 #include <stdlib.h>
 
+#include <algorithm>
 #include <random>
 #include <vector>
 
@@ -107,7 +110,21 @@ static void check_plan(const cardan_shape& s, int B, int z_sep, int flags, Count
   CHECK(P.tpc >= 1 && P.tpc <= kTokPass);
   CHECK(P.max_act >= 1 && P.max_act <= P.E && P.max_act <= P.S);
   CHECK(P.lds_routing >= (size_t)P.max_act * 16 + (size_t)4 * P.S * 4);
-  CHECK(P.lds_expert > P.lds_routing);
+  // item LDS: operand rows of the gate/up, down and (where the call has them)
+  // low-rank down tiles, the combine, the grouping scratch, T rows
+  size_t rows = 0, item = combine_lds(P) + ((P.flags & F_CB_SPLITK) ? kSplitKRed : 0);
+  for (int sp = 0; sp < P.ns; ++sp) {
+    int k0, k1;
+    joint_split(sp, P.ns, P.ns_v, KSX, KSZ, k0, k1);
+    const int x = std::min(k1, KSX) - std::min(k0, KSX), z = std::max(k1, KSX) - std::max(k0, KSX);
+    rows = std::max(rows, (size_t)(x * 4 + 1 + z * 8 + 1));
+    if (sp < P.ns_v && (P.flags & F_TBOOK)) item = std::max(item, (size_t)x * (32 / P.d) * P.K * 4);
+  }
+  rows = std::max(rows, (size_t)cdiv(KSD, P.nsd) * 8 + 1);
+  if (P.ncgr > 0) rows = std::max(rows, (size_t)cdiv(KSD, P.nsdl) * 8 + 1);
+  item = std::max({item, rows * P.nt_max * 16, (size_t)8 * P.S + 16 * P.E + 32});
+  const size_t fixed = P.lds_routing + book_bytes(P) + ((P.flags & F_XPRE) ? kXpreBytes : 0);
+  CHECK(P.lds_expert >= fixed + item && P.lds_expert < fixed + item + 256);
   if (P.flags & F_XPRE) CHECK(B == 1 && mode == 0 && P.H <= 8 * kXpreXGroups);
   if (P.flags & F_DN_WIDE) CHECK(mode == 0 && P.d == 8);
   // projection code book: code splits whose T rows fit the tile's LDS area,
@@ -201,6 +218,12 @@ int main(int argc, char** argv) {
       check_step_layout(s, B);
       plans += 9;
     }
+  }
+  // a layer that a GPU test takes for its book lines of 64 bytes
+  for (int d : {2, 8}) {
+    const cardan_shape s = {2432, 288, 100, 8, d, 256, 256};
+    snprintf(g_ctx, sizeof g_ctx, "H=2432 I=288 E=100 k=8 d=%d r=256 B=16", d);
+    CHECK(book_shift(make_plan(&s, 16, 0, F_ROUTE | F_Z | F_GROUP | F_EXPERTS)) == 2);
   }
   printf("%ld plans checked, %d failures\n", plans, g_fail);
   return g_fail ? 1 : 0;
