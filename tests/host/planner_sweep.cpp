@@ -106,6 +106,11 @@ static void check_plan(const cardan_shape& s, int B, int z_sep, int flags, Count
   CHECK(prev == KSX + KSZ);
   CHECK(P.nsd >= 1 && P.nsd <= KSD);
   if (P.r > 0 && mode == 0) CHECK(P.nsdl >= 1 && P.nsdl <= KSD);
+  // no long low-rank down tile (I/32 K-steps round to tiles of about 12, so one
+  // of up to 17 remains)
+  if (P.ncgr > 0 && !(flags & (F_BYTE_SPLITS | F_NORM_IN | F_SSQ_OUT)) && P.total < 0x80000000ull &&
+      P.lds_expert - book_bytes(P) <= kLdsMax)
+    CHECK(cdiv(KSD, P.nsdl) <= 17);
   CHECK(P.nt_max >= 1 && P.nt_max <= kTokPass && P.nt_max <= B);
   CHECK(P.tpc >= 1 && P.tpc <= kTokPass);
   CHECK(P.max_act >= 1 && P.max_act <= P.E && P.max_act <= P.S);
