@@ -2293,9 +2293,12 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2), minsize
   constexpr int SP = (VAR & kVarTwoProducts) ? kTwoProducts : 2;
   constexpr bool LINES = book_lines(D, XPRE);
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-  // the code book of the current item (BookView) at the start of dynamic LDS:
-  // a constant address, so that a read needs no addition for its base
-  uint4* cbs = reinterpret_cast<uint4*>(smem);
+  // the code book of the current item (BookView): its lines at the start of
+  // dynamic LDS, a packed one in static LDS (in dynamic LDS it measured slower:
+  // two OLMoE-shaped layers of a step at B=16 142.7 us against 138.6, at B=24
+  // 163.9 and 158.9; 160 single layers with d = 4 0.4 % on average)
+  __shared__ uint4 packed[LINES || MODE == 2 ? 1 : 256 * D / 8];
+  uint4* cbs = LINES ? reinterpret_cast<uint4*>(smem) : packed;
   warm_kernargs();
   const int tid = threadIdx.x;
   ItemTrace tr_route;

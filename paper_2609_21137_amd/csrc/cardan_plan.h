@@ -172,15 +172,17 @@ __host__ __device__ inline int tbook_groups(const Plan& P) {
 __host__ __device__ inline int expert_mode(const Plan& P) {
   return (P.flags & F_GU_DENSE) ? 2 : (P.flags & F_DN_DENSE) ? 1 : 0;
 }
-// The code book in k_expert's LDS (none for all-dense weights): 256 lines of
-// 16 << book_shift bytes, each word repeated through its line.
-__host__ __device__ inline int book_shift(const Plan& P) { return (P.flags >> kBookShiftPos) & 15; }
-__host__ __device__ inline int book_bytes(const Plan& P) {
-  return (P.flags & F_GU_DENSE) ? 0 : 256 * 16 << book_shift(P);
-}
-// Whether the kernel for block length d (xpre: batch 1) reads the book as such
-// lines, or packed (book_shift 0).
+// Whether the kernel for block length d (xpre: batch 1) reads the book as lines
+// of 16 << book_shift bytes, each word repeated through its line, or packed.
 __host__ __device__ constexpr bool book_lines(int d, bool xpre) { return d != 4 && !xpre; }
+__host__ __device__ inline int book_shift(const Plan& P) { return (P.flags >> kBookShiftPos) & 15; }
+// The kernel of two down column groups has no batch-1 form.
+__host__ __device__ inline bool book_in_lines(const Plan& P) {
+  return !(P.flags & F_GU_DENSE) && book_lines(P.d, (P.flags & (F_XPRE | F_DN_WIDE)) == F_XPRE);
+}
+// The book's lines in k_expert's dynamic LDS (a packed book is static, and
+// all-dense weights have none).
+__host__ __device__ inline int book_bytes(const Plan& P) { return book_in_lines(P) ? 256 * 16 << book_shift(P) : 0; }
 // z items of one group of tokens: (basis, 64 ranks, four splits of H).
 __host__ __device__ inline int z_items_per_group(const Plan& P) {
   return (P.z_sep ? 2 : 1) * ((P.r + 63) / 64) * P.nq_z;

@@ -335,8 +335,8 @@ Plan plan_once(const cardan_shape* s, int B, int z_sep, int flags) {
   constexpr size_t kLdsHalf = 80 * 1024 - 512;
   if ((P.flags & F_DN_WIDE) && P.lds_expert + (256 * 16 << 2) > kLdsHalf) P.flags &= ~F_DN_WIDE;
   // the longest book lines that still let two workgroups share a CU
-  if (mode != 2) {
-    int bs = book_lines(P.d, (P.flags & F_XPRE) != 0) ? kBookShiftMax : 0;
+  if (book_in_lines(P)) {
+    int bs = kBookShiftMax;
     while (bs > 0 && P.lds_expert + ((size_t)256 * 16 << bs) > kLdsHalf) --bs;
     P.flags |= bs << kBookShiftPos;
     P.lds_expert += book_bytes(P);

@@ -128,6 +128,10 @@ static void check_plan(const cardan_shape& s, int B, int z_sep, int flags, Count
   rows = std::max(rows, (size_t)cdiv(KSD, P.nsd) * 8 + 1);
   if (P.ncgr > 0) rows = std::max(rows, (size_t)cdiv(KSD, P.nsdl) * 8 + 1);
   item = std::max({item, rows * P.nt_max * 16, (size_t)8 * P.S + 16 * P.E + 32});
+  // book lines in dynamic LDS where the kernel that the plan runs reads lines
+  const bool xpre_kernel = (P.flags & F_XPRE) && !(P.flags & F_DN_WIDE);
+  CHECK(book_bytes(P) == (mode == 2 || P.d == 4 || xpre_kernel ? 0 : 4096 << book_shift(P)) &&
+        book_shift(P) <= kBookShiftMax);
   const size_t fixed = P.lds_routing + book_bytes(P) + ((P.flags & F_XPRE) ? kXpreBytes : 0);
   CHECK(P.lds_expert >= fixed + item && P.lds_expert < fixed + item + 256);
   if (P.flags & F_XPRE) CHECK(B == 1 && mode == 0 && P.H <= 8 * kXpreXGroups);
@@ -229,6 +233,12 @@ int main(int argc, char** argv) {
     const cardan_shape s = {2432, 288, 100, 8, d, 256, 256};
     snprintf(g_ctx, sizeof g_ctx, "H=2432 I=288 E=100 k=8 d=%d r=256 B=16", d);
     CHECK(book_shift(make_plan(&s, 16, 0, F_ROUTE | F_Z | F_GROUP | F_EXPERTS)) == 2);
+  }
+  {  // and one for its tiles of two column groups at batch 1
+    const cardan_shape s = {3968, 32, 32, 32, 8, 256, 256};
+    snprintf(g_ctx, sizeof g_ctx, "H=3968 I=32 E=32 k=32 d=8 r=256 B=1");
+    const Plan P = make_plan(&s, 1, 0, F_ROUTE | F_Z | F_GROUP | F_EXPERTS);
+    CHECK((P.flags & F_DN_WIDE) && (P.flags & F_XPRE));
   }
   printf("%ld plans checked, %d failures\n", plans, g_fail);
   return g_fail ? 1 : 0;

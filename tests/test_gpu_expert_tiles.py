@@ -79,6 +79,12 @@ def test_code_book_shorter_lines(C, d):
     _parity(C, 2432, 288, 100, 8, d, 256, 256, 16, seed=780)
 
 
+def test_code_book_lines_at_batch_one(C):
+    """Tiles of two column groups have no batch-1 kernel: theirs reads the book
+    as lines (the host sweep of the planner checks that this layer has them)."""
+    _parity(C, 3968, 32, 32, 32, 8, 256, 256, 1, seed=790)
+
+
 @pytest.mark.parametrize("B,k", ((1, 1), (2, 8), (3, 8), (7, 7), (8, 8), (13, 5), (16, 4), (65 // 13, 13)))
 def test_routing_tables_from_lanes(C, B, k):
     """Selections held in lanes: 1 to 64 of them, on both sides of the 16 that
