@@ -1497,6 +1497,21 @@ __device__ __forceinline__ void book_store(uint4* cb, uint4 v, int bs) {
   for (int i = 0; i <= m; ++i) cb[(c << bs) + ((i + rot) & m)] = v;
 }
 
+// The code book of the current item: lines at the start of dynamic LDS, a
+// packed book in static LDS (in dynamic LDS it measured slower: two OLMoE-shaped
+// layers of a step at B=16 142.7 us against 138.6, at B=24 163.9 and 158.9; 160
+// single layers with d = 4 0.4 % on average). The kernels of lines have no
+// static array: 16 bytes of it moved the lines and cost them 0.7 %.
+template <int D, bool DYNAMIC>
+__device__ __forceinline__ uint4* book_area(uint8_t* smem) {
+  if constexpr (DYNAMIC) {
+    return reinterpret_cast<uint4*>(smem);
+  } else {
+    __shared__ uint4 packed[256 * D / 8];
+    return packed;
+  }
+}
+
 // Gate/up tile (a, pj, cg, s): 256 output columns of projection pj over
 // split s of the joint reduction axis [x (H inputs) | z (r ranks)], i.e. the
 // VQ gather sum and V^T z accumulate in the same MFMA accumulators. Each
@@ -2293,12 +2308,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2), minsize
   constexpr int SP = (VAR & kVarTwoProducts) ? kTwoProducts : 2;
   constexpr bool LINES = book_lines(D, XPRE);
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-  // the code book of the current item (BookView): its lines at the start of
-  // dynamic LDS, a packed one in static LDS (in dynamic LDS it measured slower:
-  // two OLMoE-shaped layers of a step at B=16 142.7 us against 138.6, at B=24
-  // 163.9 and 158.9; 160 single layers with d = 4 0.4 % on average)
-  __shared__ uint4 packed[LINES || MODE == 2 ? 1 : 256 * D / 8];
-  uint4* cbs = LINES ? reinterpret_cast<uint4*>(smem) : packed;
+  uint4* cbs = book_area<D, LINES || MODE == 2>(smem);
   warm_kernargs();
   const int tid = threadIdx.x;
   ItemTrace tr_route;
@@ -2337,7 +2347,9 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2), minsize
     }
   }
   // routing tables after the book, item LDS after them
-  uint8_t* tab = smem + book_bytes(P);
+  // (book_bytes(P), as the kernel's own constants leave it: the call itself
+  // measured 1 % slower at d = 8, B = 2 to 8)
+  uint8_t* tab = smem + (!LINES || (P.flags & F_GU_DENSE) ? 0 : 256 * 16 << book_shift(P));
   uint8_t* item_smem = tab + P.lds_routing;
   const RouteTab RT = lane_routing
                           ? build_routing_lanes(P, (sel_e >= 0 && sel_e < P.E) ? sel_e : -1, sel_w, tab,
