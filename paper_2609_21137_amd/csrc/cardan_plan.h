@@ -53,7 +53,8 @@ constexpr int kPdDense = 2;   // dense K-steps in flight per wave (4 KB each)
 constexpr int kCombineChunk = 16;  // terms per load batch in the combine
 constexpr int kBookShiftMax = 3;   // the code book in LDS: 256 lines of up to 16 << kBookShiftMax bytes
 constexpr int kLrDownSteps = 4;    // K-steps of the finest low-rank down tile
-constexpr int kLrDownLong = 16;    // K-steps of the longest low-rank down tile made to keep one round of tiles
+constexpr int kLrDownLong = 16, kLrDownLong8 = 24;  // K-steps of the longest low-rank down tile made to keep
+                                                    // one round of tiles (the second: d = 8)
 constexpr int kDenseDownSteps = 24;  // most K-steps of a dense down tile of the dense-down form
 constexpr int kSplitKRed = 4 * 64 * 16 * 4;  // [4 waves][64 lanes][16] float
 // batch-1 operand area at the end of k_expert's dynamic LDS: x (H <= 4096,

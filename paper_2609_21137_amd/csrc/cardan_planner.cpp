@@ -92,11 +92,14 @@ void compressed_splits(Plan& P, double exp_act, double npj, int KSX, int KSZ, in
   P.nsdl = P.r > 0 ? std::max(1, (int)lround(KSD / 12.0)) : 1;
   const int nl_fine = P.r > 0 ? ceil_div(KSD, P.r > 128 ? 8 : kLrDownSteps) : 1;
   // (where one code tile per column group is enough, fewer low-rank tiles are
-  // tried too before a second round, but none of more than 16 K-steps: that one
-  // tile ends the down phase. H=3520, I=1024, r=504, 32 experts, B=22: one tile
-  // of 32 steps 84.9 us, three 65.9; H=1344, I=1024, r=256, up-only, B=16 61.0
-  // and 54.3)
-  const int nl_least = P.nsd == 1 ? std::min(nl_fine, ceil_div(KSD, kLrDownLong)) : nl_fine;
+  // tried too before a second round, but none of more than 16 K-steps, 24 at
+  // d = 8: that one tile ends the down phase. One tile and the usual two or
+  // three: H=3520, I=1024, r=504, 32 experts, B=22 84.9 and 65.9 us; with d = 4
+  // OLMoE B=13 to 16 67 to 71, 5 % less; H=1344, I=640, up-only, B=9 56.8 and
+  // 50.6. At d = 8 and 22 K-steps the few tiles of a second round cost as much
+  // or more: Gemma-4 B=5 44.0 and 46.7 over 20 routings)
+  const int lr_long = P.d == 8 ? kLrDownLong8 : kLrDownLong;
+  const int nl_least = P.nsd == 1 ? std::min(nl_fine, ceil_div(KSD, lr_long)) : nl_fine;
   for (int nl = nl_fine; nl >= nl_least; --nl) {
     int n = 0;
     while (KSD / (n + 1) >= 7 && exp_act * (P.ncgh * (n + 1) + P.ncgr * nl) <= kSlots) ++n;

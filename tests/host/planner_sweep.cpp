@@ -110,7 +110,7 @@ static void check_plan(const cardan_shape& s, int B, int z_sep, int flags, Count
   // of up to 17 remains)
   if (P.ncgr > 0 && !(flags & (F_BYTE_SPLITS | F_NORM_IN | F_SSQ_OUT)) && P.total < 0x80000000ull &&
       P.lds_expert - book_bytes(P) <= kLdsMax)
-    CHECK(cdiv(KSD, P.nsdl) <= 17);
+    CHECK(cdiv(KSD, P.nsdl) <= (P.d == 8 ? 24 : 17));
   CHECK(P.nt_max >= 1 && P.nt_max <= kTokPass && P.nt_max <= B);
   CHECK(P.tpc >= 1 && P.tpc <= kTokPass);
   CHECK(P.max_act >= 1 && P.max_act <= P.E && P.max_act <= P.S);
