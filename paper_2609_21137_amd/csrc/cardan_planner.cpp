@@ -38,6 +38,7 @@ int gateup_ld(int KSX, int KSZ, int ns, int ns_v) {
 size_t round256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 constexpr double kSlots = 512.0;  // nominal grid: two workgroups per CU
+constexpr double kFewTiles = 400.0, kFewTiles2 = 460.0;  // see choose_splits
 
 // Splits of the compressed gate/up tiles and of the down tiles.
 //
@@ -51,16 +52,19 @@ constexpr double kSlots = 512.0;  // nominal grid: two workgroups per CU
 // 83.8, Gemma-4 B=16 87.2 -> 75.2, OLMoE B=32 82.1 -> 74.2, wide B=2 42.3 -> 34.5
 // (1 + 1 -> 2 + 1). kCode and kLr: microseconds per K-step of a code and a
 // low-rank tile while the grid is full; kSplit: of each split's partial sums
-// in the down tiles' staging. Over 44 shapes and batches these pick the
-// fastest measured split or one within 2 % of it, but for five (3 to 7 %).
+// in the down tiles' staging.
 //
 // Down: tiles of about 24 code K-steps (16 at d = 2, which reads four words for
 // one) and 12 low-rank ones (4 KB instead of 1 KB of weights per wave and step)
 // fill many rounds evenly. While finer ones
 // fit one round, the code tiles take as many splits as do, down to 7 K-steps
 // (less than that is set-up), and the low-rank tiles 8 K-steps, or 4 where
-// their ranks fill only two waves.
-void compressed_splits(Plan& P, double exp_act, double npj, int KSX, int KSZ, int KSD, int mode) {
+// their ranks fill only two waves. Dense down tiles (16 KB per K-step) go down to
+// 8 K-steps, and to 2 while they leave half of the round free (I=480, 4 of 8
+// experts, B=1: one tile of 15 steps 23.1 us, fifteen 20.4).
+//
+// records: expected records of the routing tables (tiles of an expert's passes).
+void compressed_splits(Plan& P, double exp_act, double records, double npj, int KSX, int KSZ, int KSD, int mode) {
   const double kCode = P.d == 2 ? 0.2 : 0.13, kLr = 0.6, kSplit = 0.33;
   const double t1 = exp_act * npj * P.ncg;  // tiles with one split
   P.ns_v = P.ns = 1;
@@ -83,9 +87,13 @@ void compressed_splits(Plan& P, double exp_act, double npj, int KSX, int KSZ, in
         P.ns = nv + nl;
       }
     }
-  if (mode == 1) {  // dense down tiles, 16 KB per K-step
+  if (mode == 1) {
     P.nsd = ceil_div(KSD, kDenseDownSteps);
-    while (P.nsd < KSD && exp_act * P.ncgh * (P.nsd + 1) <= kSlots && KSD / (P.nsd + 1) >= kDenseDownSteps / 3) ++P.nsd;
+    auto fits = [&](int n) {
+      return exp_act * P.ncgh * n <= kSlots &&
+             KSD / n >= (records * P.ncgh * n <= kSlots / 2 ? 2 : kDenseDownSteps / 3);
+    };
+    while (P.nsd < KSD && fits(P.nsd + 1)) ++P.nsd;
     return;
   }
   P.nsd = std::max(1, (int)lround(KSD / (P.d == 2 ? 16.0 : 24.0)));
@@ -111,7 +119,7 @@ void compressed_splits(Plan& P, double exp_act, double npj, int KSX, int KSZ, in
   }
 }
 
-// Splits by bytes, for the all-dense layer, the stacked step and F_BYTE_SPLITS: the expected
+// Splits by bytes, for the all-dense layer, the stacked step, F_BYTE_SPLITS and calls of few tiles: the expected
 // active experts' weight bytes spread over the nominal grid, kept between 16
 // and 128 KB per tile, so small batches run every tile in one round and large
 // ones stream long tiles (a VQ down K-step counts double). Dense tiles grow to
@@ -161,6 +169,31 @@ void byte_splits(Plan& P, double exp_act, double npj, int KSX, int KSZ, int KSD,
     }
   }
   P.nsdl = std::min(P.nsdl, ceil_div(KSD, kLrDownSteps));
+}
+
+// Splits of the compressed forms: compressed_splits, but for calls of few tiles
+// the finer of those and of the splits by bytes, part by part. While few
+// workgroups are busy a tile's length is the call's: its set-up overlaps the
+// others' and costs no round. Few: the tiles split by bytes take at most 400 of
+// the 512 workgroups of a round (460 at d = 2, whose K-steps take about twice as
+// long). Measured over 1295 drawn calls and calls of the models' shapes against
+// compressed_splits alone: 138 more than 1.5 % faster (H=576, I=1792, d=2, r=232,
+// 2 of 39 experts 25.9 -> 22.5 us; H=640, I=288, d=2, r=328, 8 of 216 29.0 -> 26.1;
+// H=448, I=384, d=4, up-only, B=4 25.2 -> 22.7), six more than 1.5 % slower (2 to
+// 3.6 %).
+void choose_splits(Plan& P, double exp_act, double npj, int KSX, int KSZ, int KSD, int mode) {
+  // an expert has a record per 8 tokens: this many more if they were all in full ones
+  const double records = exp_act + std::max(0.0, P.S - exp_act) / 8.0;
+  Plan Q = P;
+  byte_splits(Q, exp_act, npj, KSX, KSZ, KSD, mode);
+  compressed_splits(P, exp_act, records, npj, KSX, KSZ, KSD, mode);
+  const double tiles = records * (npj * P.ncg * Q.ns + P.ncgh * Q.nsd + P.ncgr * Q.nsdl);
+  if (tiles > (P.d == 2 ? kFewTiles2 : kFewTiles)) return;
+  const int nl = std::max(P.ns - P.ns_v, Q.ns - Q.ns_v);
+  P.ns_v = std::max(P.ns_v, Q.ns_v);
+  P.ns = P.ns_v + nl;
+  P.nsd = std::max(P.nsd, Q.nsd);
+  P.nsdl = std::max(P.nsdl, Q.nsdl);
 }
 
 // Dynamic LDS of k_route for a plan.
@@ -224,7 +257,7 @@ Plan plan_once(const cardan_shape* s, int B, int z_sep, int flags) {
   if (by_bytes)
     byte_splits(P, exp_act, npj, KSX, KSZ, KSD, mode);
   else
-    compressed_splits(P, exp_act, npj, KSX, KSZ, KSD, mode);
+    choose_splits(P, exp_act, npj, KSX, KSZ, KSD, mode);
   // routing tables: records and four per-slot arrays (here with as many records
   // as the fewest rows of a pass could make)
   P.lds_routing = round256((size_t)std::min(P.S, P.max_act + P.S / 2) * 16 + (size_t)4 * P.S * 4);

@@ -61,6 +61,18 @@ static void check_step_layout(const cardan_shape& s, int B) {
     }
 }
 
+// a call of few tiles has no longer tiles than the splits by bytes give
+static void check_few_tiles(const cardan_shape& s, int B, int flags) {
+  const Plan P = make_plan(&s, B, 0, flags), Q = make_plan(&s, B, 0, flags | F_BYTE_SPLITS);
+  snprintf(g_ctx, sizeof g_ctx, "H=%d I=%d E=%d k=%d d=%d K=%d r=%d B=%d flags=%d few tiles", s.H, s.I, s.E, s.top_k,
+           s.d, s.K, s.r, B, flags);
+  // every selection an expert of its own, every eight a record: no more tiles than this
+  const double records = P.max_act + P.S / 8.0;
+  if (records * (n_proj(P) * P.ncg * Q.ns + P.ncgh * Q.nsd + P.ncgr * Q.nsdl) > 400.0) return;
+  CHECK(P.ns_v >= Q.ns_v && P.ns - P.ns_v >= Q.ns - Q.ns_v && P.nsd >= Q.nsd);
+  if (P.ncgr > 0) CHECK(P.nsdl >= Q.nsdl);
+}
+
 static void check_plan(const cardan_shape& s, int B, int z_sep, int flags, Counters* ref) {
   const Plan P = make_plan(&s, B, z_sep, flags);
   snprintf(g_ctx, sizeof g_ctx, "H=%d I=%d E=%d k=%d d=%d K=%d r=%d B=%d z_sep=%d flags=%d", s.H, s.I, s.E,
@@ -225,6 +237,8 @@ int main(int argc, char** argv) {
       check_plan(s, B, 0, all | F_TBOOK, &ref);
       check_plan(s, B, 1, all | F_TBOOK | F_UP_RELU2, &ref);
       check_step_layout(s, B);
+      for (int act : {0, (int)F_UP_RELU2}) check_few_tiles(s, B, all | act);
+      check_few_tiles(s, B, all | F_DN_DENSE);
       plans += 9;
     }
   }
