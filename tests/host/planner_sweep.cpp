@@ -16,6 +16,8 @@
 //     below ns_v;
 //   - the item LDS of the expert kernel holds the largest item that the call
 //     has, and no more than that;
+//   - the routing tables hold the records of every routing, a record no more
+//     rows than a pass;
 //   - sizes that must fit 32-bit offsets do;
 //   - the layers of a stack share one layout, whichever neighbours they chain
 //     to and whatever their bases.
@@ -73,6 +75,14 @@ static void check_few_tiles(const cardan_shape& s, int B, int flags) {
   if (P.ncgr > 0) CHECK(P.nsdl >= Q.nsdl);
 }
 
+// Most records that S selections of E experts make with 1 << rs rows each: an
+// expert's first selection makes one, and so do every 1 << rs after it, so with
+// all experts used the rest fills records best on one of them.
+static int most_records(int S, int E, int rs) {
+  const int used = std::min(S, E);
+  return used - 1 + (S - used + 1 + (1 << rs) - 1) / (1 << rs);
+}
+
 static void check_plan(const cardan_shape& s, int B, int z_sep, int flags, Counters* ref) {
   const Plan P = make_plan(&s, B, z_sep, flags);
   snprintf(g_ctx, sizeof g_ctx, "H=%d I=%d E=%d k=%d d=%d K=%d r=%d B=%d z_sep=%d flags=%d", s.H, s.I, s.E,
@@ -126,7 +136,23 @@ static void check_plan(const cardan_shape& s, int B, int z_sep, int flags, Count
   CHECK(P.nt_max >= 1 && P.nt_max <= kTokPass && P.nt_max <= B);
   CHECK(P.tpc >= 1 && P.tpc <= kTokPass);
   CHECK(P.max_act >= 1 && P.max_act <= P.E && P.max_act <= P.S);
-  CHECK(P.lds_routing >= (size_t)P.max_act * 16 + (size_t)4 * P.S * 4);
+  // records of the routing tables: no longer than a pass (a pass is a record
+  // wherever an expert of B distinct tokens needs several and the tables fit),
+  // and as many as the most that any routing of S selections makes
+  const int rs = record_shift(P), nrec = max_records(P);
+  if (rs != kOneRecord) {
+    CHECK(1 << rs <= P.nt_max && 2 << rs > P.nt_max && P.nt_max < B);
+  } else if (P.nt_max < B) {
+    int pass = 0;
+    while (2 << pass <= P.nt_max) ++pass;
+    const size_t tables = (size_t)std::min(P.S, P.max_act + (P.S >> pass)) * 16 + (size_t)4 * P.S * 4;
+    CHECK(((tables + 255) & ~(size_t)255) + (P.lds_expert - P.lds_routing - book_bytes(P)) > kLdsMax);
+  }
+  CHECK(P.S < 1 << kOneRecord);  // a record of kOneRecord holds every selection
+  CHECK(nrec >= most_records(P.S, P.E, rs) && (nrec <= P.S));
+  CHECK(P.lds_routing >= (size_t)nrec * 16 + (size_t)4 * P.S * 4);
+  // packed fields: expert | records << 16 of a slot, slots and records of a scan
+  CHECK(P.E < 1 << 16 && P.S < 1 << 15 && nrec < 1 << 15);
   // item LDS: operand rows of the gate/up, down and (where the call has them)
   // low-rank down tiles, the combine, the grouping scratch, T rows
   size_t rows = 0, item = combine_lds(P) + ((P.flags & F_CB_SPLITK) ? kSplitKRed : 0);
@@ -163,17 +189,17 @@ static void check_plan(const cardan_shape& s, int B, int z_sep, int flags, Count
       joint_split(sp, P.ns, P.ns_v, KSX, KSZ, k0, k1);
       CHECK(k1 <= KSX && (k1 - k0) * bps <= kTBookTileBlocks);
       CHECK((size_t)(k1 - k0) * bps * P.K * 4 <=
-            P.lds_expert - P.lds_routing - ((P.flags & F_XPRE) ? kXpreBytes : 0));
+            P.lds_expert - P.lds_routing - book_bytes(P) - ((P.flags & F_XPRE) ? kXpreBytes : 0));
     }
   } else {
     CHECK(P.n_tb == 0);
   }
   // item counts fit the kernels' int arithmetic
-  const double items = (double)P.max_act * (gateup_tiles_per_expert(P) + down_tiles_per_expert(P)) + P.n_cb;
+  const double items = (double)nrec * (gateup_tiles_per_expert(P) + down_tiles_per_expert(P)) + P.n_cb;
   CHECK(items < 2.0e9);
-  // gate/up item mapping: a bijection for several grids and active counts
+  // gate/up item mapping: a bijection for several grids and record counts
   const int n_tiles = gateup_tiles_per_expert(P);
-  const int nacts[] = {1, P.max_act, (P.max_act + 1) / 2};
+  const int nacts[] = {1, nrec, P.max_act, (P.max_act + 1) / 2};
   const int grids[] = {1, 2, 7, 256, 512, 1024};
   std::vector<unsigned char> seen;
   for (int nact : nacts) {
@@ -219,7 +245,7 @@ int main(int argc, char** argv) {
   for (const cardan_shape& s : shapes) {
     Counters ref = {(size_t)-1, 0, 0, 0, 0};
     const int all = F_ROUTE | F_Z | F_GROUP | F_EXPERTS;
-    const int batches[] = {1, 2, 3, 4, 8, 15, 16, 17, 32, 63, 64};
+    const int batches[] = {1, 2, 3, 4, 8, 9, 15, 16, 17, 32, 63, 64};
     for (int B : batches) {
       for (int z_sep = 0; z_sep < 2; ++z_sep) {
         check_plan(s, B, z_sep, all | (s.r > 0 ? 0 : 0), &ref);
@@ -236,6 +262,13 @@ int main(int argc, char** argv) {
       // projection-code-book gate/up tiles (gated and up-only)
       check_plan(s, B, 0, all | F_TBOOK, &ref);
       check_plan(s, B, 1, all | F_TBOOK | F_UP_RELU2, &ref);
+      // the scratch array's layout, and the layers of a stack (its first, a middle
+      // and its last, gated with compressed weights)
+      for (int more : {(int)F_BYTE_SPLITS, F_BYTE_SPLITS | F_UP_RELU2, (int)F_SSQ_OUT, F_NORM_IN | F_SSQ_OUT,
+                       (int)F_NORM_IN}) {
+        check_plan(s, B, 1, all | more, &ref);
+        ++plans;
+      }
       check_step_layout(s, B);
       for (int act : {0, (int)F_UP_RELU2}) check_few_tiles(s, B, all | act);
       check_few_tiles(s, B, all | F_DN_DENSE);
@@ -253,6 +286,27 @@ int main(int argc, char** argv) {
     snprintf(g_ctx, sizeof g_ctx, "H=3968 I=32 E=32 k=32 d=8 r=256 B=1");
     const Plan P = make_plan(&s, 1, 0, F_ROUTE | F_Z | F_GROUP | F_EXPERTS);
     CHECK((P.flags & F_DN_WIDE) && (P.flags & F_XPRE));
+  }
+  // layers that GPU tests take for the tiles of two column groups of a large
+  // batch, for a stack's passes of four rows, and for their LDS
+  const int all = F_ROUTE | F_Z | F_GROUP | F_EXPERTS;
+  for (int relu2 = 0; relu2 < 2; ++relu2)
+    for (int H : {512, 576}) {
+      const cardan_shape s = {H, relu2 ? 1280 : 1024, 96, 8, 8, 256, relu2 ? 136 : 24};
+      snprintf(g_ctx, sizeof g_ctx, "H=%d I=%d E=96 k=8 d=8 r=%d B=64", s.H, s.I, s.r);
+      const Plan P = make_plan(&s, 64, 0, all | (relu2 ? F_UP_RELU2 : 0));
+      CHECK((P.flags & F_DN_WIDE) && record_shift(P) == 3);
+    }
+  {
+    const cardan_shape s = {4416, 32, 300, 2, 8, 256, 80};
+    snprintf(g_ctx, sizeof g_ctx, "H=4416 I=32 E=300 k=2 d=8 r=80 B=16");
+    for (int chain : {(int)F_SSQ_OUT, (int)F_NORM_IN}) CHECK(record_shift(make_plan(&s, 16, 0, all | chain)) == 2);
+  }
+  const cardan_shape near[] = {{64, 672, 64, 32, 4, 256, 424}, {64, 1152, 64, 16, 2, 256, 512}, {1536, 416, 64, 29, 8, 256, 504}};
+  for (const cardan_shape& s : near) {
+    snprintf(g_ctx, sizeof g_ctx, "H=%d I=%d E=64 k=%d d=%d r=%d B=64", s.H, s.I, s.top_k, s.d, s.r);
+    const Plan P = make_plan(&s, 64, 0, all);
+    CHECK(P.lds_expert >= 76 * 1024 && P.lds_expert - book_bytes(P) <= kLdsMax);
   }
   printf("%ld plans checked, %d failures\n", plans, g_fail);
   return g_fail ? 1 : 0;

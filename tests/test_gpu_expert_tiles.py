@@ -32,9 +32,9 @@ def C():
     return cardan
 
 
-def _parity(C, H, I, E, k, d, K, r, B, seed, up_only=False):
-    print(f"[tiles] H={H} I={I} E={E} k={k} d={d} K={K} r={r} B={B} up_only={up_only}", flush=True)
-    L = synth.make_layer(H, I, E, d, K, r, seed=seed, up_only=up_only)
+def _parity(C, H, I, E, k, d, K, r, B, seed, up_only=False, hot=0):
+    print(f"[tiles] H={H} I={I} E={E} k={k} d={d} K={K} r={r} B={B} up_only={up_only} hot={hot}", flush=True)
+    L = synth.make_layer(H, I, E, d, K, r, seed=seed, up_only=up_only, hot_experts=range(hot), hot_bias=6.0)
     x = synth.make_input(H, B, seed=seed)
     act = "relu2_up" if up_only else "silu_glu"
     y_ref, idx_ref, a_ref, margin = O.moe_layer_factored(x, L, k, d, act=act)
@@ -46,6 +46,8 @@ def _parity(C, H, I, E, k, d, K, r, B, seed, up_only=False):
     torch.cuda.synchronize()
     assert C.workspace_status(ws) == 0, "an in-kernel wait timed out"
     assert np.array_equal(idx.cpu().numpy(), idx_ref)
+    if hot:
+        assert np.bincount(idx_ref.ravel(), minlength=E)[:hot].min() > 8  # several passes each
     err = np.abs(y.cpu().numpy().astype(np.float64) - y_ref).max() / np.abs(y_ref).max()
     print(f"[tiles] error {err:.2e}", flush=True)
     assert err <= 2.0 ** -18 * max(10.0, math.sqrt(2 * I / math.pi)), err
@@ -177,3 +179,91 @@ def test_experts_of_several_passes(C, form, B, k, E):
     torch.cuda.synchronize()
     assert np.array_equal(idx.cpu().numpy(), idx_ref)
     assert np.abs(y.cpu().numpy() - y_ref).max() <= 4e-5 * np.abs(y_ref).max()
+
+
+@pytest.mark.parametrize("H,I,up_only", ((576, 1024, False), (512, 1024, False), (576, 1280, True), (512, 1280, True)))
+def test_wide_tiles_of_several_passes(C, H, I, up_only):
+    """Down tiles of two column groups (odd and even counts of groups; the host
+    sweep of the planner checks that these layers have them) of four experts
+    that nearly every token selects: up to eight records each."""
+    _parity(C, H, I, 96, 8, 8, 256, 136 if up_only else 24, 64, seed=900, up_only=up_only, hot=4)
+
+
+@pytest.mark.parametrize("d,B,E,k", ((8, 17, 3, 2), (4, 40, 6, 5)))
+def test_dense_down_of_several_passes(C, d, B, E, k):
+    H, I, r = 320, 160, 40
+    L = synth.make_layer(H, I, E, d, 256, r, seed=910)
+    Wd = synth.make_dense_weights(H, I, E, 910, which=("down",))["W_down"]
+    x = synth.make_input(H, B, seed=910)
+    y_ref, idx_ref, _, margin = O.moe_layer_dense_down(x, L, Wd, k, d)
+    assert np.all(margin > 1e-9) and np.bincount(idx_ref.ravel()).max() > 8
+    ws = C.new_workspace(C.make_shape(H, I, E, k, d, 256, r), B)
+    y, idx, _ = C.moe_layer_dense_down(C.make_shape(H, I, E, k, d, 256, r), C.bf16_tensor(x), C.DeviceLayer.from_numpy(L),
+                                       C.bf16_tensor(Wd), ws=ws)
+    torch.cuda.synchronize()
+    assert C.workspace_status(ws) == 0
+    assert np.array_equal(idx.cpu().numpy(), idx_ref)
+    assert np.abs(y.cpu().numpy() - y_ref).max() <= 2.0 ** -18 * max(10.0, math.sqrt(2 * I / math.pi)) * np.abs(y_ref).max()
+
+
+# the last: passes of 4 token rows (the host sweep of the planner checks it)
+@pytest.mark.parametrize("H,I,E,k,d,r,B", ((192, 96, 3, 2, 8, 40, 16), (192, 96, 5, 4, 4, 72, 33), (192, 96, 3, 2, 2, 8, 17),
+                                          (4416, 32, 300, 2, 8, 80, 16)))
+def test_step_of_several_passes(C, H, I, E, k, d, r, B):
+    """A stack of two layers whose experts take up to 33 tokens: the split
+    operands' parts as two products. The oracle of each layer takes the
+    step's own input; the second layer's is checked in the step's tests."""
+    Ls = [synth.make_layer(H, I, E, d, 256, r, seed=920, layer=l, hot_experts=range(2), hot_bias=6.0) for l in range(2)]
+    x = synth.make_input(H, B, seed=920)
+    shape = C.make_shape(H, I, E, k, d, 256, r)
+    ws = C.new_workspace(shape, B)
+    xn = torch.empty((1, B, H), dtype=torch.bfloat16, device="cuda")
+    print(f"[tiles] step H={H} I={I} E={E} k={k} d={d} r={r} B={B}", flush=True)
+    y, idx, _ = C.moe_decode_step(shape, C.bf16_tensor(x), [C.DeviceLayer.from_numpy(L) for L in Ls], 1e-6, ws=ws, x_norm=xn)
+    torch.cuda.synchronize()
+    assert C.workspace_status(ws) == 0
+    y0, idx0, _, m0 = O.moe_layer_factored(x, Ls[0], k, d)
+    y1, idx1, _, m1 = O.moe_layer_factored(C.bf16_bits(xn[0]), Ls[1], k, d)
+    assert min(m0.min(), m1.min()) > 1e-9
+    for got, ref in zip(idx.cpu().numpy(), (idx0, idx1)):
+        assert np.array_equal(got, ref) and np.bincount(ref.ravel()).max() > 8
+    tol = 2.0 ** -18 * max(10.0, math.sqrt(2 * I / math.pi))
+    assert np.abs(y.cpu().numpy() - y1).max() <= tol * np.abs(y1).max()
+    xr = O.rmsnorm(y0, 1e-6)
+    # one bf16 step, and y0's own error through the normalisation
+    assert np.all(np.abs(O.bf16_to_f64(C.bf16_bits(xn[0])) - xr) <= 2.0 ** -8 * np.abs(xr) + 2 * tol * np.abs(xr).max())
+
+
+@pytest.mark.parametrize("bad", (float("inf"), float("nan")))
+@pytest.mark.parametrize("d,r", ((8, 40), (4, 0)))
+def test_non_finite_tokens_stay_apart(C, d, r, bad):
+    """A value that is not finite reaches every output of its token (its hi and
+    lo parts are rows of one product) and no bit of another token's."""
+    H, I, B = 192, 96, 19
+    shape = C.make_shape(H, I, 1, 1, d, 256, r)
+    DL = C.DeviceLayer.from_numpy(synth.make_layer(H, I, 1, d, 256, r, seed=930))
+    x = C.bf16_tensor(synth.make_input(H, B, seed=930))
+    idx, w = torch.zeros((B, 1), dtype=torch.int32, device="cuda"), torch.ones((B, 1), device="cuda")
+    z = C.shared_proj(shape, x, DL.tensors["U_gate"], DL.tensors["U_up"]) if r else None
+    ws = C.new_workspace(shape, B)
+    ref = C.vq_lr_expert_ffn(shape, x, idx, w, z, DL, ws=ws)
+    hit = [0, 5, 7, 8, 18]
+    x2, z2 = x.clone(), z.clone() if r else None
+    for t in hit:
+        if r and t != 5:
+            z2[:, t, t] = bad
+        else:
+            x2[t, 3 * t] = bad
+    y = C.vq_lr_expert_ffn(shape, x2, idx, w, z2, DL, ws=ws)
+    torch.cuda.synchronize()
+    assert C.workspace_status(ws) == 0
+    rest = [t for t in range(B) if t not in hit]
+    assert torch.isfinite(ref).all() and torch.equal(y[rest], ref[rest])
+    assert not torch.isfinite(y[hit]).any()
+
+
+@pytest.mark.parametrize("H,I,E,k,d,r,B", ((64, 672, 64, 32, 4, 424, 64), (64, 1152, 64, 16, 2, 512, 64),
+                                          (1536, 416, 64, 29, 8, 504, 64)))
+def test_layers_near_the_lds_limit(C, H, I, E, k, d, r, B):
+    """Large routing tables beside long tiles of many ranks: 80 to 96 KB of LDS."""
+    _parity(C, H, I, E, k, d, 256, r, B, seed=940)
