@@ -864,10 +864,14 @@ __device__ __forceinline__ void item_z_reduce(const Plan& P, const Args& A, int 
 //     MFMA takes both parts: rows 0..7 the hi parts, rows 8..15 the lo parts
 //     of the same tokens; merge_split adds the two halves of D after the run.
 //     With kTwoProducts the two parts are two products into the same
-//     accumulators (DeepSeek-V2-Lite B=8 3.4 % slower, Qwen3 B=16 0.3 %): the
-//     stacked step's form. Its layers round each other's outputs to bf16, so
-//     the order of a sum decides roundings that grow through the stack (2e-3
-//     of y after four layers), and the step keeps the order it always had.
+//     accumulators: the stacked step's form. Its layers round each other's
+//     outputs to bf16, so the order of a sum decides roundings that grow
+//     through the stack: after four Qwen3 layers at B=16 one product gives
+//     other outputs by 2.2e-3 of y and swaps 1.6 % of the selections. The step
+//     keeps its order, which costs it, two products and one per step: four
+//     Qwen3 layers at B=16 207.9 and 204.5 us, two of DeepSeek-V2-Lite at B=8
+//     152.4 and 145.0, of OLMoE at B=32 164.7 and 162.4, of Gemma-4 at B=16
+//     173.9 and 168.8.
 //   W (weights): lane l holds rows 32 ks + 8 g .. + 8 of output column
 //     c0 + 4 n + q for MFMA q = 0..3. For VQ weights this slice is one code
 //     word (d = 8) or two (d = 4) read from the LDS code book; for dense bf16
@@ -1069,41 +1073,39 @@ struct VqPipe {
 // Two 64-column sub-tiles per wave, kColsPerGroup columns apart (a down tile
 // of two column groups, float32 activations as bf16 hi + lo): each K-step's
 // activation reads serve both sub-tiles. A second sub-tile past n_out reads
-// zeros (its results are never stored).
-template <int D, int NOPS, int PD, bool LINES>
+// zeros (its results are never stored). For d = 8, the one block length whose
+// plans have such tiles.
+template <int NOPS, int PD, bool LINES>
 struct VqPipe2 {
-  static constexpr int W = D == 8 ? 1 : 2;
-  uint32_t buf[PD][2 * W];
+  static constexpr int D = 8;
+  uint32_t buf[PD][2];
   rsrc_t rs;
-  uint32_t lane_off, lane_off2, step_bytes, row_len;
+  uint32_t lane_off, lane_off2, step_bytes;
   int ks0, nks;
   bool has2;
 
-  __device__ __forceinline__ void load(int i, uint32_t (&b)[2 * W]) {
+  __device__ __forceinline__ void load(int i, uint32_t (&b)[2]) {
     const uint32_t st = (uint32_t)(ks0 + i) * step_bytes;
     const uint32_t o = i < nks ? lane_off + st : kOob, o2 = i < nks && has2 ? lane_off2 + st : kOob;
     b[0] = __builtin_amdgcn_raw_buffer_load_b32(rs, o, 0, 0);
-    if constexpr (D == 4) b[1] = __builtin_amdgcn_raw_buffer_load_b32(rs, o + row_len, 0, 0);
-    b[W] = __builtin_amdgcn_raw_buffer_load_b32(rs, o2, 0, 0);
-    if constexpr (D == 4) b[W + 1] = __builtin_amdgcn_raw_buffer_load_b32(rs, o2 + row_len, 0, 0);
+    b[1] = __builtin_amdgcn_raw_buffer_load_b32(rs, o2, 0, 0);
   }
   __device__ __forceinline__ void prime(const uint8_t* c, int n_rows, int rl, int c0, int n_out, int k0,
                                         int k1) {
     rs = make_rsrc(c, (uint32_t)n_rows * rl);
-    row_len = rl;
     const int g = (threadIdx.x & 63) >> 4;
     const int col = min(c0 + 4 * (threadIdx.x & 15), n_out - 4);
     const int col2 = min(c0 + kColsPerGroup + 4 * (threadIdx.x & 15), n_out - 4);
     has2 = c0 + kColsPerGroup < n_out;
     step_bytes = (uint32_t)(32 / D) * rl;
-    lane_off = (uint32_t)(g * (8 / D)) * rl + col;
-    lane_off2 = (uint32_t)(g * (8 / D)) * rl + col2;
+    lane_off = (uint32_t)g * rl + col;
+    lane_off2 = (uint32_t)g * rl + col2;
     ks0 = k0;
     nks = k1 - k0;
 #pragma unroll
     for (int u = 0; u < PD; ++u) load(u, buf[u]);
   }
-  __device__ __forceinline__ void step(int ks, const uint32_t (&b)[2 * W], const BookView<D, LINES>& cb,
+  __device__ __forceinline__ void step(int ks, const uint32_t (&b)[2], const BookView<D, LINES>& cb,
                                        const uint4* __restrict__ ops, int ops_ld, int ops_ks0, int nt,
                                        f32x4 acc[8]) {
     const int oi = a_index<NOPS>(threadIdx.x & 63, nt, ops_ld, ks - ops_ks0);
@@ -1114,7 +1116,7 @@ struct VqPipe2 {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       w[q] = cb.word(b, q);
-      w[4 + q] = cb.word(b + W, q);
+      w[4 + q] = cb.word(b + 1, q);
     }
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
@@ -1122,7 +1124,7 @@ struct VqPipe2 {
       if constexpr (NOPS == kTwoProducts) acc[q] = mfma_bf16(a1, w[q], acc[q]);
     }
     constexpr int T = NOPS == kTwoProducts ? 2 : 1;
-    sched_step<T + (D == 8 ? 8 : 16), 8 * T>();
+    sched_step<T + 8, 8 * T>();
   }
   __device__ __forceinline__ void run(const BookView<D, LINES>& cb, const uint4* ops, int ops_ld, int ops_ks0, int nt,
                                       f32x4 acc[8]) {
@@ -1722,8 +1724,8 @@ __device__ __forceinline__ void item_gateup(const Plan& P, const Args& A, const 
     trace_mark(2);
   }
 
-  // counts the tile done for (a, cg); the down tiles form p from the
-  // n_proj ns partial sums of their columns
+  // counts the tile done for (expert, cg), one count for all of its records;
+  // the down tiles form p from the n_proj ns partial sums of their columns
   publish(wsp<int>(A, P.o_gu_tick) + (R.e * P.ncg + cg) * kTickPad);
 }
 
@@ -1746,6 +1748,9 @@ __device__ __forceinline__ void stage_p_ns(const WsAccess& ws, const Plan& P, ui
     stage_p<1, 8, RELU2>(ws, P, ps, ld, nt, nquad, slot0, col0);
 }
 
+// (a is not read here: without the parameter the compiler inlines the down
+// tiles another way, and the kernels measured 0.3 % slower, the stacked step of
+// four Qwen3 layers at B=16 217.6 -> 220.2 us)
 template <bool RELU2, int SP, typename Prime, typename Stage, typename Run, typename Dst>
 __device__ __forceinline__ void down_body(const Plan& P, const Args& A, const Routing& R, int a, int ks0, int ks1,
                                           int c0, int n_out, Prime prime, Stage stage, Run run, Dst dst,
@@ -1832,16 +1837,17 @@ __device__ void item_down_vq(const Plan& P, const Args& A, const RouteTab& RT, i
 
 // VQ down tile over two column groups (cgx, cgx + 1): as item_down_vq, each
 // wave on 64 columns of both groups.
-template <int D, bool LINES, int SP, bool RELU2>
+template <bool LINES, int SP, bool RELU2>
 __device__ void item_down_vq2(const Plan& P, const Args& A, const RouteTab& RT, int a, int cgx, int s,
                               uint4* cbs, uint8_t* smem) {
+  constexpr int D = 8;
   const Routing R = expert_of(P, RT, a);
   const int H = P.H, I = P.I, S = P.S, KS = I / 32;
   const int ks0 = s * KS / P.nsd, ks1 = (s + 1) * KS / P.nsd;
   const int c0 = cgx * kColsPerGroup + (threadIdx.x >> 6) * 64;
   const uint8_t* codes = A.L.codes_down + (size_t)R.e * (I / D) * H;
   float* dn = wsp<float>(A, P.o_dn) + (size_t)s * S * H;
-  VqPipe2<D, SP, kPdVqWide, LINES> pipe;
+  VqPipe2<SP, kPdVqWide, LINES> pipe;
   uint4 bk;
   down_body_wide<RELU2, SP, 8>(P, A, R, a, ks0, ks1,
                [&]() {
@@ -1866,9 +1872,8 @@ __device__ void item_down_vq2(const Plan& P, const Args& A, const RouteTab& RT, 
   }
 }
 
-// Low-rank down tile (a, cgr, s): partial A_e^T p over split s of I. The
-// last of the expert's ncgr * nsdl tiles sums the splits into u_e[slot]
-// (r values per slot) and flags the expert's low-rank part done.
+// Low-rank down tile (a, cgr, s): partial A_e^T p over split s of I, r values
+// per slot. The combine sums the nsdl partials of u_e itself.
 template <int SP, bool RELU2>
 __device__ void item_down_lr(const Plan& P, const Args& A, const RouteTab& RT, int a, int cgr, int s,
                              uint8_t* smem) {
@@ -1882,7 +1887,6 @@ __device__ void item_down_lr(const Plan& P, const Args& A, const RouteTab& RT, i
   down_body<RELU2, SP>(P, A, R, a, ks0, ks1, c0, r, [&]() { pipe.prime(Ae, r, c0, r, I, ks0, ks1); }, [&]() {},
             [&](const uint4* ps, int ld, int nt, f32x4* acc) { pipe.run(ps, ld, ks0, nt, acc); },
             [&](int slot) { return uap + ((size_t)s * S + slot) * r; }, smem);
-  // the combine sums the nsdl partials of u_e itself
   publish(wsp<int>(A, P.o_dn_done) + (R.e * (P.ncgh + 1) + P.ncgh) * kTickPad);
 }
 
@@ -2430,7 +2434,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2), minsize
       if constexpr (MODE != 0)
         item_down_dense<RELU2>(P, A, RT, a, rem / P.nsd, rem % P.nsd, item_smem);
       else if constexpr (DNW == 2)
-        item_down_vq2<D, LINES, SP, RELU2>(P, A, RT, a, rem / P.nsd * 2, rem % P.nsd, cbs, item_smem);
+        item_down_vq2<LINES, SP, RELU2>(P, A, RT, a, rem / P.nsd * 2, rem % P.nsd, cbs, item_smem);
       else
         item_down_vq<D, LINES, SP, RELU2>(P, A, RT, a, rem / P.nsd, rem % P.nsd, cbs, item_smem);
       tr.done(A, P, P.n_pre + jp, 5);

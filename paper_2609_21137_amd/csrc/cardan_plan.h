@@ -21,8 +21,8 @@
 //                   joint axis [H inputs | r ranks]), partial sums; the down
 //                   tiles form p = silu(g) * u from them (up-only experts: up
 //                   tiles alone, p = relu(u)^2)
-//   down tiles      (a, 256 output columns of [H | r], split of I); the last
-//                   low-rank tile of an expert sums its splits into u_e
+//   down tiles      (a, 256 output columns of [H | r], split of I), partial
+//                   sums: the combine adds the splits of u_e too
 //   combine tiles   (256 output columns, group of tpc tokens)
 // Every k_expert workgroup first groups the selections by expert in its own
 // LDS (the routing tables), so items look up experts and slots in LDS.
