@@ -2414,7 +2414,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2), minsize
           continue;
         }
       }
-      constexpr int PDC = DNW == 2 ? kPdGateUpWide : kPdGateUp;
+      constexpr int PDC = DNW == 2 ? kPdGateUpWide : D == 2 ? kPdGateUp2 : kPdGateUp;
       if constexpr (XPRE) {
         const KernArgs& K = kern_args();
         item_gateup<D, DNW == 2, LINES, XPRE, SP, PDC>(K.P, K.A, RT, t.a, t.pj, t.cg, t.s, lr_first, cbs, item_smem,

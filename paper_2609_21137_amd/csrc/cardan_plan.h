@@ -47,6 +47,10 @@ constexpr int kPdVqWide = 8;  // the same in the down tiles of two column groups
                               // codes per wave: measured faster than 12 and 16 steps at batch 16)
 constexpr int kPdGateUp = 8;  // the same for gate/up tiles: half the bytes requested at once when
                               // every tile starts together, the rest as the first steps complete
+constexpr int kPdGateUp2 = 4;  // the same at d = 2, whose steps are four code rows: with 8 the kernels spilled (Qwen3
+                               // with d = 2 at B=16 79.2 us, 76.6 with 4; the dense-down layer at B=4 48.4 and 46.2;
+                               // H=384, I=1120, r=496, B=2 dense-down 26.4 and 24.9, layer 30.8 and 29.0; 6 and 7
+                               // steps do not spill either but gain half of it)
 constexpr int kPdGateUpWide = 16;  // gate/up code steps in flight in the large-batch kernel: 4 KB of
                                    // codes per wave, the bytes in flight HBM needs when every tile streams
 constexpr int kPdDense = 2;   // dense K-steps in flight per wave (4 KB each)

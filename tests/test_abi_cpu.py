@@ -49,6 +49,25 @@ def test_abi_version(C):
     assert int(m.group(1)) == C.abi_version()
 
 
+def test_kernels_do_not_spill(C, tmp_path):
+    """No kernel of the built library keeps vector registers in scratch memory
+    (its loads and stores would sit in the expert tiles' pipelines)."""
+    from paper_2609_21137_amd import build
+    llvm = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin")
+    fat, obj = str(tmp_path / "fat"), str(tmp_path / "obj")
+    tools = [[f"{llvm}/llvm-objcopy", f"--dump-section=.hip_fatbin={fat}", build.LIB, str(tmp_path / "copy")],
+             [f"{llvm}/clang-offload-bundler", "--type=o", "--unbundle", f"--input={fat}", f"--output={obj}",
+              "--targets=hipv4-amdgcn-amd-amdhsa--gfx950"],
+             [f"{llvm}/llvm-readelf", "--notes", obj]]
+    for cmd in tools:
+        if not os.path.exists(cmd[0]):
+            pytest.skip(f"{cmd[0]} not installed")
+        notes = subprocess.run(cmd, capture_output=True, text=True, check=True).stdout
+    spills = re.findall(r"\.vgpr_spill_count:\s+(\d+)", notes)
+    assert len(spills) == notes.count(".vgpr_count:") >= 60
+    assert set(spills) == {"0"}, [m for m in re.findall(r"\.symbol:\s+(\S+)[\s\S]*?spill_count:\s+(\d+)", notes) if m[1] != "0"]
+
+
 def _ws(C, shape, B):
     n = ctypes.c_size_t(0)
     rc = C.lib().cardan_workspace_bytes(ctypes.byref(shape), B, ctypes.byref(n))
