@@ -136,7 +136,7 @@ void byte_splits(Plan& P, double exp_act, double npj, int KSX, int KSZ, int KSD,
   const double tile_max = (mode != 0 && nominal > 2 * 128.0 * 1024 ? 512.0 : 128.0) * 1024;
   double tile = fmin(tile_max, fmax(16.0 * 1024, nominal));
   auto splits = [&](double bytes, int max_splits) {
-    return std::max(1, std::min(max_splits, (int)lround(bytes / tile)));
+    return std::max(1, std::min(max_splits, (int)(bytes / tile + 0.5)));
   };
   for (;;) {
     if (tile >= 0.75 * (code_bytes + lr_bytes)) {
@@ -184,11 +184,14 @@ void byte_splits(Plan& P, double exp_act, double npj, int KSX, int KSZ, int KSD,
 void choose_splits(Plan& P, double exp_act, double npj, int KSX, int KSZ, int KSD, int mode) {
   // an expert has a record per 8 tokens: this many more if they were all in full ones
   const double records = exp_act + std::max(0.0, P.S - exp_act) / 8.0;
+  const double few = P.d == 2 ? kFewTiles2 : kFewTiles;
+  compressed_splits(P, exp_act, records, npj, KSX, KSZ, KSD, mode);
+  // (more tiles than that with one split each: no need to see the splits by bytes)
+  if (records * (npj * P.ncg + P.ncgh + P.ncgr) > few) return;
   Plan Q = P;
   byte_splits(Q, exp_act, npj, KSX, KSZ, KSD, mode);
-  compressed_splits(P, exp_act, records, npj, KSX, KSZ, KSD, mode);
   const double tiles = records * (npj * P.ncg * Q.ns + P.ncgh * Q.nsd + P.ncgr * Q.nsdl);
-  if (tiles > (P.d == 2 ? kFewTiles2 : kFewTiles)) return;
+  if (tiles > few) return;
   const int nl = std::max(P.ns - P.ns_v, Q.ns - Q.ns_v);
   P.ns_v = std::max(P.ns_v, Q.ns_v);
   P.ns = P.ns_v + nl;
